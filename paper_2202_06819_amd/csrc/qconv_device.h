@@ -82,8 +82,8 @@ struct EpiParams {
     bool fast;
 };
 
-template <int FK>
-__device__ __forceinline__ void finish_epilogue_params(const ConvArgs &a, EpiParams<FK> &ep) {
+template <int FK, class Args>
+__device__ __forceinline__ void finish_epilogue_params(const Args &a, EpiParams<FK> &ep) {
     const int e = 32 - a.shift - a.acc_shift;
     bool ok = e >= 0;
     if (ok && e > 0) {
@@ -102,8 +102,8 @@ __device__ __forceinline__ void finish_epilogue_params(const ConvArgs &a, EpiPar
 // From multipliers already in registers (mraw[i] for channel cb + i, every
 // entry a valid multiplier: channels past k repeat the last one and are never
 // stored).
-template <int FK>
-__device__ __forceinline__ void make_epilogue_params(const ConvArgs &a, const int32_t (&mraw)[4 * FK],
+template <int FK, class Args>
+__device__ __forceinline__ void make_epilogue_params(const Args &a, const int32_t (&mraw)[4 * FK],
                                                      EpiParams<FK> &ep) {
 #pragma unroll
     for (int i = 0; i < 4 * FK; ++i) ep.mul[i] = mraw[i];
@@ -165,8 +165,8 @@ __device__ __forceinline__ void add_bias(const ConvArgs &a, v4i (&acc)[FP][FK], 
 
 // The residual words of one pixel's channel run (the same words store_run
 // writes); zeros for a pixel past the output.
-template <int BITS, int FK>
-__device__ __forceinline__ void load_run(const ConvArgs &a, int m, int cb, uint32_t *words) {
+template <int BITS, int FK, class Args>
+__device__ __forceinline__ void load_run(const Args &a, int m, int cb, uint32_t *words) {
     constexpr int CPW = 32 / BITS;
     constexpr int NWD = 4 * FK / CPW;
 #pragma unroll
@@ -210,8 +210,8 @@ __device__ __forceinline__ int32_t clamp_med3(int32_t x, int32_t lo, int32_t hi)
 }
 
 // Store one pixel's packed channel run (4*FK channels of `BITS` bits).
-template <int BITS, int FK>
-__device__ __forceinline__ void store_run(const ConvArgs &a, int m, int cb, const uint32_t *words) {
+template <int BITS, int FK, class Args>
+__device__ __forceinline__ void store_run(const Args &a, int m, int cb, const uint32_t *words) {
     constexpr int CPW = 32 / BITS;
     constexpr int NWD = 4 * FK / CPW;
     uint32_t *yw = reinterpret_cast<uint32_t *>(a.yptr + (size_t)m * (a.k * BITS / 8) + cb * BITS / 8);
@@ -235,8 +235,8 @@ __device__ __forceinline__ void store_run(const ConvArgs &a, int m, int cb, cons
 // Fast requantisation (see EpiParams): one v_mad_i64_i32, one v_med3_i32 and
 // one shift-or per value.  A non-negative clamp range needs no mask: the
 // clamped value already fits its field.
-template <int BITS, int FP, int FK, bool UNSIGNED_OUT, bool RES>
-__device__ __forceinline__ void epilogue_fast(const ConvArgs &a, v4i (&acc)[FP][FK], int mbase, int cb, int l16,
+template <int BITS, int FP, int FK, bool UNSIGNED_OUT, bool RES, class Args>
+__device__ __forceinline__ void epilogue_fast(const Args &a, v4i (&acc)[FP][FK], int mbase, int cb, int l16,
                                               const EpiParams<FK> &ep) {
     constexpr int CPW = 32 / BITS;
     constexpr int NWD = 4 * FK / CPW;
@@ -274,8 +274,8 @@ __device__ __forceinline__ void epilogue_fast(const ConvArgs &a, v4i (&acc)[FP][
 // cb + 4*tm + v of pixel mbase + 16*tn + l16.
 // EXT: the kernel supports a bias (already in the accumulators, see init_acc)
 // and a residual; without it neither is looked at.
-template <int BITS, int FP, int FK, bool EXT>
-__device__ __forceinline__ void epilogue(const ConvArgs &a, v4i (&acc)[FP][FK], int mbase, int cb, int l16,
+template <int BITS, int FP, int FK, bool EXT, class Args>
+__device__ __forceinline__ void epilogue(const Args &a, v4i (&acc)[FP][FK], int mbase, int cb, int l16,
                                          const EpiParams<FK> &ep) {
     constexpr int CPW = 32 / BITS;   // channels per 32-bit word
     constexpr int NWD = 4 * FK / CPW;

@@ -2,6 +2,7 @@
 // Validation and sizing touch no device and run on any machine; only the
 // launch paths call the HIP runtime.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdarg.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -651,6 +652,42 @@ void fill_args(ConvArgs &a, const qconv_desc *d, const qconv_layout_info &li, co
     a.acc_shift = d->bits == 4 ? 4 * (d->x_signed + d->w_signed) : 0;
 }
 
+// The f32 requantiser of a layer's epilogue (FloatEpilogue), where its
+// conditions hold: a clamp over a whole output range (effective bounds lo, hi)
+// and sums that stay within 2^24 whatever the operands.
+FloatEpilogue float_epilogue(const qconv_desc *d, const qconv_layout_info &li, const qconv_epilogue *epi, int32_t lo,
+                             int32_t hi) {
+    FloatEpilogue f{};
+    const int as = d->bits == 4 ? 4 * (d->x_signed + d->w_signed) : 0;
+    const int64_t most = (int64_t)1 << 24, worst = li.max_abs_acc << as;
+    if (worst > most) return f;
+    const bool res = epi->residual != nullptr, rs = epi->residual_signed != 0;
+    const bool unsigned_out = lo == 0;
+    int s;
+    float offset;
+    if (d->bits == 4) {
+        if (!((lo == 0 && hi == 15) || (lo == -8 && hi == 7)) || (res && rs == unsigned_out)) return f;
+        s = 4;
+        offset = unsigned_out ? 0.5f : 8.5f;
+        f.out_xor = unsigned_out ? 0u : 0x88888888u;
+        f.res_xor = rs ? 0x88888888u : 0x08080808u;
+    } else {
+        if (!((lo == -128 && hi == 127) || (lo == 0 && hi == 127))) return f;
+        s = unsigned_out ? 1 : 0;
+        offset = (unsigned_out ? 0.5f : 128.5f) - (res && rs ? 128.0f : 0.0f);
+        f.out_shift = s;
+        f.out_mask = unsigned_out ? 0x7F7F7F7Fu : 0xFFFFFFFFu;
+        f.out_xor = unsigned_out ? 0u : 0x80808080u;
+        f.res_xor = rs ? 0x80808080u : 0u;
+        f.res_scale = (float)(1 << s);
+    }
+    f.kind = 1;
+    f.scale = ldexpf(1.0f, s - epi->shift - as);
+    f.addend = offset * (float)(1 << s);
+    f.bias_room = (uint32_t)((most - worst) >> as);
+    return f;
+}
+
 // Kernels that stage more than 64 KiB of LDS must opt in, once per device.
 // Workgroups of `kernel` (threads, dynamic LDS bytes) that fit one CU, as the
 // runtime reports them; 0 if it cannot say.  Asked once per device and shape:
@@ -699,11 +736,256 @@ int auto_xcd_order(const qconv_layout_info &li, const Plan &pl, int64_t filter_b
     return channel_major < pixel_major ? 2 : 1;
 }
 
+// How a prepared wide layer runs on the direct kernels: wave tile (32-channel
+// pairs, 16-pixel fragments), waves per output tile and tiles per workgroup,
+// steps in flight, filters resident in LDS.  np 0: not at all.
+struct DirectChoice {
+    int np = 0, fp = 1, wd = 1, wt = 1, la = 9, resident = 0;
+};
+
+bool direct_lin(const qconv_desc *d) {
+    return d->r == 1 && d->s == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 && d->pad_w == 0;
+}
+
+// ---- when a prepared layer runs on the direct kernels.  A launch time is
+// estimated for the wide tile's plan and for each wave tile below as a sum of
+// terms (us) in what the launch does, and the direct kernels take the layer
+// where their best estimate is clearly lower.  The coefficients are least-squares
+// fits to about 1,080 random layers (1x1 to 5x5, strides 1 and 2, 16 to 2048
+// channels, 7 to 112 pixels a side, batch 1 to 256, both widths), each timed
+// with every wave tile and with the wide tile a caller would take; the
+// estimates' errors are 12-17 %.  What they say: a wide launch pays 0.5-0.75 us
+// for every stage its workgroups walk in turn, a direct one 0.05-0.3 us for each
+// step of its waves, but loads every operand of every step through the L1, so
+// that few stages and much work favour the wide kernels.
+struct DirectCandidate {
+    int lin;
+    DirectChoice c;
+    float us[8];
+};
+constexpr DirectCandidate kDirectCandidates[] = {
+    // lin np fp wd wt la resident   us: base, round, step, traffic / round x waves, MFMA, MB, filter MB, epilogue
+    {0, {1, 1, 1, 1, 9, 0}, {2.74f, 0.0f, 0.0569f, 0.0204f, 0.0682f, 0.0652f, 0.0f, 0.0f}},
+    {0, {1, 1, 2, 1, 9, 0}, {2.89f, 0.0f, 0.0713f, 0.00606f, 0.0997f, 0.12f, 0.0422f, 0.0f}},
+    {0, {1, 1, 4, 1, 9, 0}, {2.55f, 0.0f, 0.132f, 0.0206f, 0.0583f, 0.139f, 0.219f, 0.0f}},
+    {0, {1, 1, 8, 1, 9, 0}, {1.63f, 0.0f, 0.309f, 0.00792f, 0.101f, 0.214f, 0.303f, 0.0f}},
+    {0, {1, 2, 1, 1, 3, 0}, {3.04f, 0.0f, 0.0867f, 0.0114f, 0.0618f, 0.0987f, 0.0f, 0.0f}},
+    {0, {1, 2, 4, 1, 3, 0}, {2.94f, 0.0f, 0.227f, 0.0487f, 0.00889f, 0.114f, 0.0f, 0.0207f}},
+    {0, {2, 2, 1, 1, 3, 0}, {3.42f, 0.0f, 0.122f, 0.0103f, 0.0331f, 0.0435f, 0.0f, 0.0911f}},
+    {0, {2, 2, 2, 1, 3, 0}, {3.83f, 0.0f, 0.14f, 0.0104f, 0.0428f, 0.0804f, 0.0f, 0.102f}},
+    {0, {2, 2, 4, 1, 3, 0}, {3.24f, 0.0f, 0.27f, 0.0218f, 0.0276f, 0.0754f, 0.0f, 0.205f}},
+    {0, {2, 2, 1, 4, 3, 1}, {4.32f, 0.0f, 0.105f, 0.0899f, 0.0f, 0.0704f, 1.56f, 0.0f}},
+    {0, {2, 2, 1, 8, 3, 1}, {4.62f, 0.0f, 0.272f, 0.0f, 0.0f, 0.109f, 0.429f, 0.0f}},
+    {1, {1, 1, 1, 1, 4, 0}, {0.0f, 0.0f, 0.698f, 0.0256f, 0.0657f, 0.096f, 1.13f, 0.0f}},
+    {1, {1, 1, 1, 1, 8, 0}, {2.46f, 0.0f, 0.0533f, 0.0055f, 0.1f, 0.102f, 0.305f, 0.0f}},
+    {1, {1, 1, 2, 1, 8, 0}, {2.58f, 0.0f, 0.0789f, 0.00597f, 0.0878f, 0.169f, 0.46f, 0.0f}},
+    {1, {1, 1, 4, 1, 8, 0}, {0.0f, 0.0f, 0.437f, 0.00324f, 0.0951f, 0.233f, 0.497f, 0.0f}},
+    {1, {1, 2, 1, 1, 4, 0}, {0.0f, 0.0f, 0.728f, 0.0178f, 0.0626f, 0.0878f, 1.0f, 0.0f}},
+    {1, {1, 2, 1, 1, 8, 0}, {2.57f, 0.0f, 0.0711f, 0.00888f, 0.0629f, 0.118f, 0.519f, 0.0f}},
+    {1, {2, 2, 1, 1, 4, 0}, {3.09f, 0.0f, 0.0876f, 0.0531f, 0.0f, 0.046f, 0.112f, 0.0f}},
+    {1, {2, 2, 2, 1, 4, 0}, {3.59f, 0.0f, 0.121f, 0.052f, 0.00376f, 0.0425f, 0.108f, 0.0f}},
+    {1, {2, 4, 1, 1, 4, 0}, {3.41f, 0.0f, 0.156f, 0.0409f, 0.0236f, 0.0541f, 0.116f, 0.00547f}},
+    {1, {2, 2, 1, 4, 1, 1}, {3.12f, 0.0f, 0.0f, 0.147f, 0.0f, 0.181f, 10.1f, 0.0f}},
+    {1, {2, 2, 1, 4, 2, 1}, {3.13f, 0.0f, 0.098f, 0.0771f, 0.0f, 0.168f, 4.49f, 0.0f}},
+    {1, {2, 2, 1, 4, 4, 1}, {3.01f, 0.0f, 0.213f, 0.0445f, 0.0f, 0.0871f, 3.24f, 0.0f}},
+};
+// us of a wide launch: base, stage, MFMA, band, epilogue, MB, filter MB, any-size filter, split, shared SIMD, MFMA of one wave
+constexpr float kWideCost[2][11] = {
+    {2.92f, 0.753f, 0.0059f, 0.222f, 0.0669f, 0.0f, 0.238f, 0.0133f, 2.08f, 0.0192f, 0.00426f},
+    {2.93f, 0.512f, 0.011f, 0.186f, 0.0582f, 0.0471f, 0.173f, 0.0f, 3.49f, 0.029f, 0.00407f},
+};
+// (end of the fitted costs)
+
+// MB of packed operands, as the estimates count them
+struct RouteSizes {
+    double x_mb, y_mb, w_mb, b;   // b: KB of a pixel fragment's step
+    int64_t steps;
+};
+
+double wide_estimate(const qconv_desc *d, const qconv_tile_info &t, const Plan &pl, const RouteSizes &z, int lin) {
+    const int64_t nchunks = (d->c + t.chunk_c - 1) / t.chunk_c, tiles = pl.mtiles * pl.ktiles;
+    const int64_t waves = t.threads / 64, ks = t.chunk_c / 64, rs = (int64_t)d->r * d->s;
+    const int64_t resident = kNumCUs * std::max<int64_t>(1, std::min<int64_t>(kLdsBytes / std::max<int64_t>(pl.lds, 1), 16 / waves));
+    const int64_t wgs = tiles * pl.splits, cps = pl.splits > 1 ? pl.cps : nchunks;
+    const int64_t act = std::min(wgs, resident), walks = (wgs + act - 1) / act, stages = walks * cps;
+    const double wps = std::max(1.0, (double)act * waves / 1024.0);   // waves per SIMD
+    const double mfma = (double)rs * ks * t.frag_p * t.frag_k;
+    const double band = (double)pl.rows * (d->w + 2 * d->pad_w) / (64.0 * waves) * ks * 2.0 * z.b;
+    const double epi = (double)walks * t.frag_p * t.frag_k;
+    const bool fixed = (d->r == 3 && d->s == 3) || rs == 1;
+    const double f[11] = {1.0, (double)stages, stages * mfma * wps, stages * band * wps, epi * wps, z.x_mb + z.y_mb,
+                          z.w_mb, fixed ? 0.0 : stages * mfma * wps, pl.splits > 1 ? 1.0 : 0.0,
+                          wps > 1.0 ? (double)stages : 0.0, stages * mfma};
+    double us = 0.0;
+    for (int i = 0; i < 11; ++i) us += kWideCost[lin][i] * f[i];
+    return us;
+}
+
+double direct_estimate(const qconv_desc *d, int64_t m, const RouteSizes &z, const DirectCandidate &k) {
+    const DirectChoice &c = k.c;
+    const int64_t kb = (d->k + 32 * c.np - 1) / (32 * c.np), mt = (m + 16 * c.fp - 1) / (16 * c.fp);
+    const int64_t s = (z.steps + c.wd - 1) / c.wd, sr = (s + c.la - 1) / c.la * c.la;
+    double f[8] = {1.0};
+    if (c.resident) {
+        const int64_t lds = sr * 2 * c.np * 1024;
+        if (lds > kLdsBytes) return 1e30;
+        const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(12 / c.wt, kLdsBytes / lds));
+        const int64_t wgs = std::max<int64_t>(1, std::min<int64_t>((mt + c.wt - 1) / c.wt, kNumCUs * per_cu / kb));
+        const double rounds = (double)((mt + wgs * c.wt - 1) / (wgs * c.wt));
+        const double wps = std::max(1.0, (double)wgs * kb * c.wt / 1024.0);
+        f[1] = rounds;
+        f[2] = rounds * sr;
+        f[3] = rounds * sr * wps;
+        f[4] = rounds * wps;
+        f[5] = z.x_mb + z.y_mb;
+        f[6] = sr / 1000.0 * wgs * kb / 256.0 * c.np * 64 / c.wt;   // filling LDS
+    } else {
+        const double t = (double)kb * mt;
+        f[1] = (double)sr / c.la;
+        f[2] = (double)sr;
+        f[3] = t * c.wd * sr / 1024.0 * (2 * c.np + c.fp * z.b);
+        f[4] = t * c.wd * sr / 1024.0 * c.np * c.fp;
+        f[5] = z.x_mb + z.y_mb;
+        f[6] = z.w_mb;
+        f[7] = t * c.np * c.fp / 1024.0;
+    }
+    double us = 0.0;
+    for (int i = 0; i < 8; ++i) us += k.us[i] * f[i];
+    return us;
+}
+
+DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_tile_info &t, const Plan &pl,
+                           int64_t filter_bytes, bool proj) {
+    const int lin = direct_lin(d) ? 1 : 0;
+    if (!lin && d->c % 64 != 0 && d->c > 64) return DirectChoice();
+    const RouteSizes z{li.x_bytes / 1e6, li.y_packed_bytes / 1e6, filter_bytes / 1e6, d->bits / 8.0,
+                       (int64_t)d->r * d->s * ((d->c + 63) / 64)};
+    const DirectChoice none;
+    const DirectCandidate *best = nullptr;
+    double best_us = 1e30;
+    for (const DirectCandidate &k : kDirectCandidates) {
+        if (k.lin != lin || (proj && k.c.resident) || k.c.wd > z.steps) continue;
+        // some are compiled for one round of their steps in flight, some for several only
+        const int64_t wave_steps = (z.steps + k.c.wd - 1) / k.c.wd;
+        if (lin && wave_steps > k.c.la && (k.c.la < 4 || (k.c.la == 4 && k.c.np == 1))) continue;
+        if (!lin && k.c.la == 3 && wave_steps <= 3) continue;
+        const double us = direct_estimate(d, li.m, z, k);
+        if (us < best_us) {
+            best_us = us;
+            best = &k;
+        }
+    }
+    // The margin covers the estimates' errors; long launches of larger filters
+    // are where a wrong choice costs most (up to 1.6x) and the wide kernels are
+    // at their best.  A projection costs a wide launch less than a direct one
+    // (it rides on staged pixels): 20 % against about 35 % at batch 16.
+    const double margin = (lin ? 1.1 : 1.15 + 0.01 * best_us) * (proj ? 1.15 : 1.0);
+    return best && best_us * margin < wide_estimate(d, t, pl, z, lin) ? best->c : none;
+}
+
+// One job of a direct launch (its epilogue comes later): filter r x s with
+// padding (ph, pw), the first tap `tap0` of the image.
+void direct_job(const qconv_desc *d, const qconv_layout_info &li, const DirectArgs &a, DirectJob &j, const void *x,
+                int r, int s, int ph, int pw, int tap0, int wd) {
+    const int64_t back = ((int64_t)ph * d->w + pw) * a.xpix;
+    const int cb = 64 * d->bits / 8;
+    j.x = static_cast<const uint8_t *>(x) - back;
+    j.xrange = (int32_t)(li.x_bytes + back);
+    j.r = r; j.s = s; j.ph = ph; j.pw = pw;
+    j.padded = ph > 0 || pw > 0;
+    j.taps = r * s;
+    j.steps = j.taps * ((d->c + 63) / 64);
+    j.xs_row = (d->w - s + 1) * a.xpix;
+    j.xs_chunk = cb - ((r - 1) * d->w + s - 1) * a.xpix;
+    j.ws0 = tap0 * a.tk16;
+    j.ws_chunk = 4 * a.psw - (j.taps - 1) * a.tk16;
+    j.steps_per_wave = (j.steps + wd - 1) / wd;
+    j.div_s = make_fastdiv((uint32_t)s);
+    j.div_taps = make_fastdiv((uint32_t)j.taps);
+}
+
+struct DirectLaunch {
+    const DirectInstance *inst = nullptr;
+    int64_t grid = 0, lds = 0;
+    int threads = 0;
+};
+
+// The direct launch of a prepared layer as `c` says; false if it does not fit.
+// Every field but the epilogues' is filled in.  The kernels' offsets are 31-bit
+// and their tap masks 32-bit words with one bit taken; a filter larger than 1x1
+// (or strided or padded) needs whole 64-channel chunks.
+bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_tile_info &t, const Plan &pl, bool ext,
+                 int64_t filter_bytes, const void *x, const void *w, bool proj, const DirectChoice &c, DirectArgs &a,
+                 DirectLaunch &out) {
+    const int64_t taps = (int64_t)d->r * d->s, xpix = (int64_t)d->c * d->bits / 8;
+    const int64_t back = ((int64_t)d->pad_h * d->w + d->pad_w) * xpix;
+    if (c.np == 0 || d->nb > 1 || taps > 31) return false;
+    if (li.x_bytes + 2 * back + ((int64_t)d->r * d->w + d->s + 2) * xpix >= (1ll << 31)) return false;
+    const bool lin = direct_lin(d);
+    if (!lin && d->c % 64 != 0 && d->c > 64) return false;
+    const int64_t steps = taps * ((d->c + 63) / 64), wave_steps = (steps + c.wd - 1) / c.wd;
+    out.inst = direct_instance(d->bits, t.frag_k, c.np, c.fp, ext, c.la, wave_steps > c.la, lin, c.resident);
+    if (!out.inst) return false;
+    memset(&a, 0, sizeof(a));
+    a.w = static_cast<const uint8_t *>(w);
+    a.wbytes = (int32_t)filter_bytes;
+    a.h_in = d->h; a.w_in = d->w; a.k = d->k; a.m = (int32_t)li.m; a.p = li.p; a.pq = li.p * li.q; a.q = li.q;
+    a.sh = d->stride_h; a.sw = d->stride_w;
+    a.xpix = (int32_t)xpix;
+    a.psw = (int32_t)pl.pstride_w;
+    a.tk16 = t.tile_k * 16;
+    a.kt_stride = (int32_t)((d->c + t.chunk_c - 1) / t.chunk_c * (t.chunk_c / 16) * pl.pstride_w);
+    a.wk = t.waves_k;
+    a.pairs = (int32_t)(pl.ktiles * t.tile_k / 32);
+    const int need_pairs = (d->k + 16 * t.frag_k - 1) / (16 * t.frag_k) * (t.frag_k / 2);   // a block holds frag_k / 2 pairs
+    a.kblocks = (need_pairs + c.np - 1) / c.np;
+    a.mtiles = (a.m + 16 * c.fp - 1) / (16 * c.fp);
+    a.tiles = a.kblocks * a.mtiles;
+    a.wd = c.wd;
+    a.wt = c.wt;
+    direct_job(d, li, a, a.job[0], x, d->r, d->s, d->pad_h, d->pad_w, 0, c.wd);
+    a.div_pq = make_fastdiv((uint32_t)a.pq);
+    a.div_q = make_fastdiv((uint32_t)a.q);
+    a.div_wk = make_fastdiv((uint32_t)a.wk);
+    a.div_kb = make_fastdiv((uint32_t)a.kblocks);
+    a.div_mt = make_fastdiv((uint32_t)a.mtiles);
+    a.div_wd = make_fastdiv((uint32_t)a.wd);
+    a.acc_shift = d->bits == 4 ? 4 * (d->x_signed + d->w_signed) : 0;
+    out.threads = 64 * c.wd * c.wt;
+    if (c.resident) {
+        if (c.wd != 1 || proj) return false;
+        out.lds = (steps + c.la - 1) / c.la * c.la * 2 * c.np * 1024;
+        if (out.lds > kLdsBytes || ensure_lds_attribute(out.inst->kernel, out.lds) != QCONV_OK) return false;
+        const int per_cu = std::max(1, occupancy_per_cu(out.inst->kernel, out.threads, out.lds));
+        const int64_t want = (a.mtiles + c.wt - 1) / c.wt;
+        const int64_t wgs = std::min<int64_t>(want, std::max<int64_t>(1, (int64_t)kNumCUs * per_cu / a.kblocks));
+        a.walk = (int32_t)(wgs * c.wt);
+        out.grid = wgs * a.kblocks;
+        a.job_groups = (int32_t)out.grid;
+    } else {
+        out.lds = c.wd > 1 ? (int64_t)2 * c.np * c.fp * c.wd * 1024 : 0;
+        if (out.lds > kLdsBytes || (c.wd > 1 && c.wt > 1) || out.threads > 512) return false;
+        const int64_t k = std::min<int64_t>(a.kblocks, 8);
+        a.pixel_fast = a.kblocks > 1 && filter_bytes + k * li.x_bytes < 8 * filter_bytes + li.x_bytes;
+        out.grid = (a.tiles + c.wt - 1) / c.wt;
+        a.job_groups = (int32_t)out.grid;
+        if (proj) {
+            // the projection's tiles follow: a 1x1 filter on the centre tap's pixels
+            direct_job(d, li, a, a.job[1], x, 1, 1, 0, 0, (int)taps, c.wd);
+            if (a.job[1].steps_per_wave > c.la && !out.inst->multi) return false;
+            out.grid *= 2;
+        }
+    }
+    return out.grid > 0 && out.grid < (1ll << 31);
+}
+
 // The convolution; w is packed KRSC filters (prepared == false) or the
 // prepared filters of tile_id (prepared == true, w_bytes_given bytes).
 // splits > 1 (prepared filters only): split-K over channel chunks with its
 // workspace in `workspace`.
 // wg_per_cu, band_buffers, xcd_order: the launch knobs of a qconv_schedule.
+// direct_ok: the layer may run on the direct kernels instead (no launch knob is
+// forced).
 // x_nchw (then x is unused): int8 N x C x H x W activations, packed on the way
 // by the tile's fused instance, which also writes the packed copy to x_packed
 // when that is not null.
@@ -712,7 +994,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
              int32_t splits, void *stream, int32_t wg_per_cu = 0, int32_t band_buffers = 0,
              int32_t xcd_order = -1, int32_t ablation = 0, const int8_t *x_nchw = nullptr,
              void *x_packed = nullptr, bool noalloc = false, const qconv_epilogue *epi_proj = nullptr,
-             void *y_proj = nullptr) {
+             void *y_proj = nullptr, bool direct_ok = false) {
     qconv_layout_info li;
     qconv_desc kd;
     int rc = kernel_desc(d, &kd, &li);
@@ -886,6 +1168,37 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
         if (pc > 0 || use_one) {
             rc = plan_tile(d, li, te.info, &pl, pc > 0 ? pc : 0, 1, use_one, ablation, proj);
             if (rc) return rc;
+        }
+    }
+    if (direct_ok && te.info.variant == QCONV_VARIANT_WIDE) {
+        DirectArgs da;
+        DirectLaunch dl;
+        const DirectChoice dc = choose_direct(d, li, te.info, pl, wb, proj);
+        if (plan_direct(d, li, te.info, pl, ext, wb, x, w, proj, dc, da, dl)) {
+            da.mode = requant ? QCONV_OUT_REQUANT : QCONV_OUT_RAW_I32;
+            da.res = requant ? static_cast<const uint8_t *>(epi->residual) : nullptr;
+            da.res_signed = requant ? epi->residual_signed : 0;
+            auto job_epilogue = [&](DirectJob &j, const qconv_epilogue *e, void *out) {
+                j.yptr = static_cast<uint8_t *>(out);
+                if (!requant) return;
+                j.mult = e->mult;
+                j.bias = e->bias;
+                j.shift = e->shift;
+                j.hi = e->clamp_hi;
+                j.lo = std::min(e->relu ? std::max(e->clamp_lo, 0) : e->clamp_lo, j.hi);
+                j.fe = float_epilogue(d, li, e, j.lo, j.hi);   // (a projection's sums are below the layer's bound)
+            };
+            job_epilogue(da.job[0], epi, y);
+            if (proj) job_epilogue(da.job[1], epi_proj, y_proj);
+            rc = ensure_lds_attribute(dl.inst->kernel, dl.lds);
+            if (rc) return rc;
+            hipError_t e = dl.inst->launch(da, dim3((unsigned)dl.grid), dl.threads, (size_t)dl.lds, (hipStream_t)stream);
+            if (e != hipSuccess) return fail(QCONV_EHIP, "conv launch (%s): %s", te.info.name, hipGetErrorString(e));
+            g_last_launch.grid = dl.grid;
+            g_last_launch.threads = dl.threads;
+            g_last_launch.lds = dl.lds;
+            snprintf(g_last_launch.kernel, sizeof(g_last_launch.kernel), "%s", te.info.name);
+            return QCONV_OK;
         }
     }
     ConvArgs a;
@@ -1083,14 +1396,14 @@ int qconv2d_prepared(const qconv_desc *d, const void *x, const void *w_prepared,
                      size_t workspace_bytes, void *stream) {
     g_err[0] = 0;
     return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, workspace, workspace_bytes, tile_id, splits,
-                    stream);
+                    stream, 0, 0, -1, 0, nullptr, nullptr, false, nullptr, nullptr, true);
 }
 
 int qconv2d_prepared_noalloc(const qconv_desc *d, const void *x, const void *w_prepared, size_t w_prepared_bytes,
                              const qconv_epilogue *epi, void *y, int32_t tile_id, int32_t splits, void *stream) {
     g_err[0] = 0;
     return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, nullptr, 0, tile_id, splits, stream, 0, 0, -1, 0,
-                    nullptr, nullptr, true);
+                    nullptr, nullptr, true, nullptr, nullptr, true);
 }
 
 // The tile a layer with a fused projection runs (tile_id, or the built-in
@@ -1198,7 +1511,7 @@ int qconv2d_proj(const qconv_desc *d, const void *x, const void *w_prepared, siz
     g_err[0] = 0;
     if (!y_proj) return fail(QCONV_EINVAL, "y_proj must be non-NULL");
     return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, workspace, workspace_bytes, tile_id, splits,
-                    stream, 0, 0, -1, 0, nullptr, nullptr, false, epi_proj, y_proj);
+                    stream, 0, 0, -1, 0, nullptr, nullptr, false, epi_proj, y_proj, true);
 }
 
 int qconv_noalloc_limits(int64_t *scratch_bytes, int64_t *max_tiles) {

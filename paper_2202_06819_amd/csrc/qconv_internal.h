@@ -35,6 +35,19 @@ __host__ __device__ inline uint32_t fdiv(uint32_t n, FastDiv f) {
     return (t + n) >> f.shr;
 }
 
+// The f32 requantiser of an epilogue (EpiParams in qconv_device.h); kind 0: not
+// used (the clamp is not a whole output range, or an accumulator may pass 2^24).
+struct FloatEpilogue {
+    int32_t kind;
+    float scale;        // 2^(s - shift - acc_shift)
+    float addend;       // (0.5 + offset) * 2^s (8-bit: also takes back the residual's offset)
+    uint32_t bias_room; // largest |bias| that keeps a sum within 2^24
+    uint32_t res_xor;   // residual bytes: sign offset (and the half for 4 bits)
+    float res_scale;    // 2^s for 8-bit residuals
+    int32_t out_shift;  // packed bytes to values: shift, mask, sign offset
+    uint32_t out_mask, out_xor;
+};
+
 // Everything a convolution launch needs, passed by value as the kernel argument.
 struct ConvArgs {
     const uint8_t *xptr;    // packed activations, N x H x W x C
@@ -100,6 +113,44 @@ struct ConvArgs {
     int32_t shift2, lo2, hi2;
 };
 
+// One convolution of a direct launch (qconv_direct.h): the layer, or the 1x1
+// projection that shares its input and filter image.
+struct DirectJob {
+    const uint8_t *x;       // packed activations, moved back by the padding (row ph, column pw of the padded image)
+    uint8_t *yptr;          // output (raw int32 or packed)
+    const int32_t *mult;    // per-channel multipliers (requant mode)
+    const int32_t *bias;    // per-channel accumulator offsets, or null
+    int32_t xrange;         // buffer-load range
+    int32_t r, s, ph, pw, padded;
+    int32_t taps, steps;    // r * s; taps times 64-channel chunks
+    int32_t xs_row, xs_chunk;   // input offset from the last tap of a row, of a chunk, to the next step
+    int32_t ws0, ws_chunk;      // image offset of the first tap, and from a chunk's last tap to the next step
+    int32_t steps_per_wave;
+    int32_t shift, lo, hi;
+    FastDiv div_s, div_taps;
+    FloatEpilogue fe;
+};
+
+// The argument of a direct convolution launch.
+struct DirectArgs {
+    DirectJob job[2];       // [1]: the projection
+    const uint8_t *w;       // prepared filter image
+    const uint8_t *res;     // residual in y's packed layout, or null (job 0)
+    int32_t wbytes;
+    int32_t h_in, w_in, k, m, p, pq, q, sh, sw;
+    int32_t xpix;           // bytes per input pixel
+    int32_t psw, tk16, kt_stride;   // image: bytes per granule plane, per tap, per channel tile
+    int32_t wk;             // channel blocks of an image's channel tile
+    int32_t pairs;          // 32-channel pairs of the image
+    int32_t kblocks, mtiles, tiles;   // wave tiles along channels, pixels, and their product
+    int32_t job_groups;     // workgroups of job 0 (the projection's follow)
+    int32_t pixel_fast;     // tiles numbered pixel fastest (else channel fastest)
+    int32_t wd, wt;         // waves per tile (depth), tiles per workgroup
+    int32_t walk;           // resident: pixel tiles between two of a wave
+    FastDiv div_pq, div_q, div_wk, div_kb, div_mt, div_wd;
+    int32_t mode, acc_shift, res_signed;
+};
+
 // Band pixels one thread of a wide tile stages per channel chunk: the 4
 // packed 16-byte vectors every thread prefetches, or more for tiles whose
 // pixel count reaches the thread count (their band of zero-padded rows can
@@ -144,6 +195,14 @@ struct TileEntry {
     FixedInstance fused;    // 3x3 instance reading int8 NCHW activations (the pack fused in), or empty
 };
 
+// A direct convolution kernel: image fragments per block, 32-channel pairs and
+// 16-pixel fragments per wave, steps in flight, filters resident in LDS.
+struct DirectInstance {
+    int bits, fkb, np, fp, ext, la, multi, lin, resident;
+    hipError_t (*launch)(const DirectArgs &, dim3 grid, int threads, size_t lds_bytes, hipStream_t);
+    const void *kernel;
+};
+
 // A kernel with some of the techniques switched off (for measurement).
 struct AblationInstance {
     const char *tile;       // the tile it is a variant of
@@ -169,6 +228,9 @@ const AblationInstance *ablation_instance(const char *tile_name, int mask);
 
 // Defined in qconv_tiles_proj.hip.
 const ProjInstance *proj_instance(const char *tile_name);
+
+// Defined in qconv_direct.hip.
+const DirectInstance *direct_instance(int bits, int fkb, int np, int fp, int ext, int la, int multi, int lin, int resident);
 
 // Defined in qconv_pack.hip.
 hipError_t launch_pack(const int8_t *src, void *dst, int32_t n, int32_t c, int32_t h, int32_t w, int32_t bits,

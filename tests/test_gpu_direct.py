@@ -1,0 +1,167 @@
+"""Prepared layers that run on the direct kernels: small layers at the edges of
+their tiles (pixel fragments, channel pairs and chunks, padding wider than the
+filter, the end of the tensor) and every form of their epilogue, from the
+filter image of every wide tile, against the oracle's sums."""
+import numpy as np
+import pytest
+
+import oracle
+import qconv_inputs as qi
+from _util import announce, assert_same, oracle_threads
+
+pytestmark = pytest.mark.gpu
+
+# (n, h, w, c, k, r, s, stride, pad, bits)
+SHAPES = [
+    (1, 1, 1, 32, 8, 1, 1, 1, 0, 4),        # one pixel, half a chunk
+    (1, 3, 5, 64, 24, 1, 1, 1, 0, 4),       # 15 pixels
+    (1, 4, 4, 96, 40, 1, 1, 1, 0, 4),       # 16 pixels, a chunk and a half: the last load ends at the tensor's end
+    (1, 1, 17, 160, 72, 1, 1, 1, 0, 4),     # 17 pixels
+    (3, 9, 7, 256, 64, 1, 1, 1, 0, 4),
+    (2, 11, 5, 512, 136, 1, 1, 1, 0, 4),    # several rounds of steps
+    (2, 9, 9, 128, 32, 1, 1, 2, 0, 4),      # strided 1x1
+    (1, 7, 7, 32, 64, 3, 3, 1, 1, 4),       # half a chunk under a 3x3
+    (2, 7, 18, 64, 72, 3, 3, 1, 1, 4),      # rows of more than one fragment
+    (1, 14, 14, 128, 40, 3, 3, 2, 1, 4),
+    (1, 5, 6, 64, 8, 3, 3, 1, 4, 4),        # padding wider than the filter
+    (1, 7, 7, 512, 64, 3, 3, 1, 1, 4),      # depth over eight waves
+    (1, 9, 8, 64, 24, 5, 5, 1, 2, 4),
+    (1, 10, 9, 64, 16, 4, 7, 1, 3, 4),      # 28 taps
+    (1, 9, 9, 64, 16, 6, 6, 1, 2, 4),       # 36 taps: more than a mask holds
+    (1, 5, 3, 16, 4, 1, 1, 1, 0, 8),
+    (1, 3, 11, 80, 20, 1, 1, 1, 0, 8),
+    (1, 7, 7, 48, 20, 3, 3, 1, 1, 8),
+    (2, 8, 8, 64, 36, 3, 3, 2, 1, 8),
+    (3, 6, 7, 320, 160, 1, 1, 1, 0, 8),
+]
+
+
+def _requant(acc, mult, shift, lo, hi, bias=None, res=None):
+    a = acc.astype(object) if shift > 40 else acc.astype(np.int64)
+    if bias is not None:
+        a = a + bias
+    t = (a * mult + (1 << (shift - 1))) >> shift
+    if res is not None:
+        t = t + res
+    return np.clip(t.astype(np.int64) if shift <= 40 else np.array(t, dtype=np.int64), lo, hi)
+
+
+def _pack(y, bits):
+    if bits == 8:
+        return y.astype(np.int8)
+    y = (y & 15).astype(np.uint32).reshape(*y.shape[:-1], -1, 8)
+    return np.bitwise_or.reduce(y << (4 * np.arange(8, dtype=np.uint32)), axis=-1).astype(np.uint32)
+
+
+def _forms(g, k, bits, spread, y_shape):
+    """(name, arguments) of the epilogues: both output ranges, a clamp inside
+    one, multipliers past 24 bits, extreme shifts, and biases and residuals of
+    either signedness."""
+    mult = g.integers(1 << 14, 1 << 15, size=k).astype(np.int32)
+    span = 8 if bits == 4 else 64
+    sh = int(max(1, min(40, round(np.log2(max(spread, 1) * 2 ** 14.5 / span)))))
+    full = (0, 15) if bits == 4 else (-128, 127)
+    other = (-8, 7) if bits == 4 else (0, 127)
+    signed = mult * g.choice([-1, 1], size=k).astype(np.int32)
+    res_u = g.integers(0, 16 if bits == 4 else 256, size=y_shape)
+    res_s = g.integers(-8 if bits == 4 else -128, 8 if bits == 4 else 128, size=y_shape)
+    return [
+        ("full range", dict(mult=mult, shift=sh, clamp=full)),
+        ("other range", dict(mult=signed, shift=sh, clamp=other)),
+        ("inside a range", dict(mult=mult, shift=sh, clamp=(1, 6))),
+        ("wide multipliers", dict(mult=(mult.astype(np.int64) * 40000).clip(max=2 ** 31 - 1).astype(np.int32),
+                                  shift=min(sh + 15, 62), clamp=full)),
+        ("shift 1", dict(mult=np.ones(k, np.int32), shift=1, clamp=other)),
+        ("shift 62", dict(mult=mult, shift=62, clamp=full)),
+        ("bias", dict(mult=mult, shift=sh, clamp=full, bias=g.integers(-300, 300, size=k).astype(np.int32))),
+        ("bias past the f32 form", dict(mult=mult, shift=sh, clamp=full,
+                                        bias=g.integers(-(1 << 22), 1 << 22, size=k).astype(np.int32))),
+        ("unsigned residual", dict(mult=mult, shift=sh, clamp=full, res=res_u, res_signed=False)),
+        ("signed residual and bias", dict(mult=signed, shift=sh, clamp=other, res=res_s, res_signed=True,
+                                          bias=g.integers(-300, 300, size=k).astype(np.int32))),
+        ("residual of the other signedness", dict(mult=mult, shift=sh, clamp=full, res=res_s, res_signed=True)),
+    ]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_direct_layers(shape):
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    n, h, w, c, k, r, s, stride, pad, bits = shape
+    dev = torch.device("cuda:0")
+    g = np.random.default_rng([77, *shape])
+    signed = bits == 8
+    xr, wr = (qi.S8, qi.S8) if signed else (qi.U4, qi.S4)
+    L = qi.Layer("direct", n, h, w, c, k, r, s, stride, pad, bits, signed, True, xr, wr)
+    d = L.desc()
+    x = g.integers(xr[0], xr[1] + 1, size=(n, c, h, w)).astype(np.int8)
+    wt = g.integers(wr[0], wr[1] + 1, size=(k, c, r, s)).astype(np.int8)
+    acc = oracle.qconv_layer(x, wt, bits=bits, x_signed=signed, w_signed=True, stride=(stride, stride), pad=(pad, pad),
+                             threads=oracle_threads())["acc"].reshape(n, L.p, L.q, k)
+    xp = q.pack(torch.from_numpy(x).to(dev), bits, signed)
+    wp = q.pack(torch.from_numpy(wt).to(dev), bits, True)
+    forms = _forms(g, k, bits, float(np.abs(acc).mean()), acc.shape)
+    direct = 0
+    for t in q.tiles():
+        if t["variant"] != 2 or q.tile_status(d, t["id"]) != 0:
+            continue
+        prep = q.prepare_filters(d, wp, t["id"])
+        announce(f"direct {shape} {t['name']} raw")
+        y = q.conv2d(d, xp, prep, tile=t["id"], prepared=True)
+        torch.cuda.synchronize()
+        launch = q.last_launch()
+        direct += launch["lds_bytes"] == 0 or launch["threads"] != t["threads"]
+        assert_same(y.cpu().numpy(), acc.astype(np.int32), f"{shape} {t['name']} raw")
+        for name, f in forms:
+            if t["frag_p"] != 2 and "residual" not in name and name != "full range":
+                continue   # the epilogue depends on the image's frag_k only
+            announce(f"direct {shape} {t['name']} {name}")
+            kw = dict(requant=True, mult=torch.from_numpy(f["mult"]).to(dev), shift=f["shift"], relu=False,
+                      clamp=f["clamp"])
+            if "bias" in f:
+                kw["bias"] = torch.from_numpy(f["bias"]).to(dev)
+            if "res" in f:
+                packed = _pack(f["res"], bits)
+                kw.update(residual=torch.from_numpy(packed.view(np.int32) if bits == 4 else packed).to(dev),
+                          residual_signed=f["res_signed"])
+            y = q.conv2d(d, xp, prep, tile=t["id"], prepared=True, **kw)
+            torch.cuda.synchronize()
+            want = _pack(_requant(acc, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f.get("bias"),
+                                  f.get("res")), bits)
+            assert_same(y.cpu().numpy(), want, f"{shape} {t['name']} {name}")
+    assert direct or r * s > 31, "no tile took the direct kernels"
+
+
+def test_direct_projection():
+    """The strided 3x3 and its projection in one direct launch, against the two
+    layers run apart by the wide kernels (a forced launch knob keeps them there)."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    dev = torch.device("cuda:0")
+    for bits, n, h, c, k in ((4, 1, 14, 64, 72), (4, 2, 9, 256, 64), (8, 1, 11, 128, 36)):
+        L = qi.Layer("proj", n, h, h, c, k, 3, 3, 2, 1, bits, bits == 8, True)
+        d, dp = L.desc(), q.proj_desc(L.desc())
+        g = np.random.default_rng([78, n, h, c, k])
+        lo, hi = (0, 15) if bits == 4 else (-128, 127)
+        x = q.pack(torch.from_numpy(g.integers(lo, hi + 1, size=(n, c, h, h)).astype(np.int8)).to(dev), bits, bits == 8)
+        w3 = q.pack(torch.from_numpy(g.integers(-8, 8, size=(k, c, 3, 3)).astype(np.int8)).to(dev), bits, True)
+        w1 = q.pack(torch.from_numpy(g.integers(-8, 8, size=(k, c, 1, 1)).astype(np.int8)).to(dev), bits, True)
+        m3, m1 = (torch.from_numpy(g.integers(1 << 14, 1 << 15, size=k).astype(np.int32)).to(dev) for _ in range(2))
+        b1 = torch.from_numpy(g.integers(-200, 200, size=k).astype(np.int32)).to(dev)
+        for t in q.tiles():
+            if q.proj_tile_status(d, t["id"]) != 0 or q.tile_status(dp, t["id"]) != 0:
+                continue
+            announce(f"direct projection {bits} {n} {h} {c} {k} {t['name']}")
+            y, yp = q.ProjConv2dCall(d, x, q.prepare_filters_proj(d, w3, w1, t["id"]), tile=t["id"], requant=True,
+                                     mult=m3, shift=22, relu=False, clamp=(lo, hi),
+                                     proj=dict(mult=m1, shift=20, relu=False, clamp=(lo, hi), bias=b1))()
+            sch = dict(tile_id=t["id"], wg_per_cu=1)
+            w = [q.Conv2dCall(d, x, q.prepare_filters(d, w3, t["id"]), requant=True, mult=m3, shift=22, relu=False,
+                              clamp=(lo, hi), schedule=sch)(),
+                 q.Conv2dCall(dp, x, q.prepare_filters(dp, w1, t["id"]), requant=True, mult=m1, shift=20, relu=False,
+                              clamp=(lo, hi), bias=b1, schedule=sch)()]
+            torch.cuda.synchronize()
+            assert_same(y.cpu().numpy(), w[0].cpu().numpy(), f"projection {t['name']} layer")
+            assert_same(yp.cpu().numpy(), w[1].cpu().numpy(), f"projection {t['name']} projection")
