@@ -1147,6 +1147,22 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
             if (hits(x, xin_bytes) || hits(w, wb) || hits(y, ybytes) || (wsb > 0 && hits(workspace, wsb)))
                 return fail(QCONV_EINVAL, "x_packed overlaps another operand");
         }
+        // Where a workgroup runs several stages, each stages its band from NCHW
+        // again (every halo row, and every channel tile the whole input):
+        // measured on 326 random layers, pack and convolution apart take 0.9-1.1
+        // times the fused launch at two stages with rows of whole dwords, 0.25-0.7
+        // times it from three stages on or with other rows (N=5 57x57 512->96:
+        // 84.6 us fused, 7.0 + 17.6 apart), and up to 1.5 times it at one stage.
+        // The packed copy is then the convolution's input.
+        const int64_t wgs = std::min<int64_t>(pl.grid, pl.mtiles * pl.ktiles);
+        const int64_t stages = (pl.mtiles * pl.ktiles + wgs - 1) / wgs * pl.cps;
+        if (x_packed && (stages > 2 || (stages == 2 && d->w % 4 != 0))) {
+            hipError_t e = launch_pack(x_nchw, x_packed, d->n, d->c, d->h, d->w, d->bits, d->x_signed, 1,
+                                       (hipStream_t)stream);
+            if (e != hipSuccess) return fail(QCONV_EHIP, "pack launch: %s", hipGetErrorString(e));
+            return run_conv(d, x_packed, w, prepared, w_bytes_given, epi, y, nullptr, 0, tile_id, 1, stream, wg_per_cu,
+                            band_buffers, xcd_order, ablation, nullptr, nullptr, false, nullptr, nullptr, true);
+        }
         launch = te.fused.launch;
         kernel = te.fused.kernel;
         single = &te.fused;
