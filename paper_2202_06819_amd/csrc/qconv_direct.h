@@ -72,15 +72,11 @@ __device__ __forceinline__ float byte_f32(uint32_t w) {
 // joins in the fma's addend.
 template <int BITS, int FP, int FK, bool RES>
 __device__ __forceinline__ void epilogue_f32(const DirectEpilogue &a, const FloatEpilogue &fe, v4i (&acc)[FP][FK],
-                                             int mbase, int cb, int l16, const float (&mul)[4 * FK]) {
+                                             int mbase, int cb, int l16, const float (&mul)[4 * FK],
+                                             const uint32_t (&rw)[FP][4 * FK * BITS / 32]) {
     constexpr int CPW = 32 / BITS;
     constexpr int NWD = 4 * FK / CPW;
     const float c0 = fe.addend;
-    uint32_t rw[FP][RES ? NWD : 1];
-    if constexpr (RES) {
-#pragma unroll
-        for (int tn = 0; tn < FP; ++tn) load_run<BITS, FK>(a, mbase + tn * 16 + l16, cb, rw[tn]);
-    }
 #pragma unroll
     for (int tn = 0; tn < FP; ++tn) {
         uint32_t words[NWD];
@@ -129,8 +125,14 @@ __device__ __forceinline__ void epilogue_f32(const DirectEpilogue &a, const Floa
 
 // FKB: fragments per channel block of the image (the tile's frag_k).  LA: steps
 // in flight; MULTI: a wave has more than LA steps (at least two rounds of LA).
-// LIN: a 1x1 filter at stride 1 without padding.
-template <int BITS, int FKB, int NP, int FP, bool EXT, int LA, bool MULTI, bool LIN, bool WRES>
+// LIN: a 1x1 filter at stride 1 without padding.  B16 (4 bits): steps come in
+// pairs, 128 channels, and a lane loads the 16 bytes of both at once, 32
+// consecutive channels (its granules are 2 gq and 2 gq + 1); for channels in whole
+// 128s.  (On 3x3 layers it changes little: 14.3 -> 14.7 us at 28x28 128->128 N=64,
+// 21.2 -> 18.0 at 14x14 256->256, where the wide kernels take 13.3 and 11.9.)  The loads, not the arithmetic, bound these kernels: 1x1 256->64 at 56x56
+// N=64 takes 9.2 us with them and 12.1 with 8-byte loads, 2048->512 at 7x7 9.6 and
+// 12.6.
+template <int BITS, int FKB, int NP, int FP, bool EXT, int LA, bool MULTI, bool LIN, bool WRES, bool B16 = false>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) conv_direct(DirectArgs a) {
     constexpr int NF = 2 * NP;                       // MFMA rows of 16 channels per wave
     constexpr bool WHOLE = FKB == 4 && NP == 2;      // the wave's channels are one image block
@@ -138,7 +140,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
     constexpr int NBK = NF / FE;
     constexpr int CB = 64 * BITS / 8;                // bytes of a step's channels of one pixel
     constexpr int AS = WRES && LA % 2 == 0 ? 2 : LA; // filter fragment sets
-    using Raw = std::conditional_t<BITS == 4, u32x2, u32x4>;
+    static_assert(!B16 || (BITS == 4 && LIN && WRES && LA % 2 == 0), "two steps a load: 4-bit resident 1x1");
+    constexpr int US = B16 ? 2 : 1;                  // steps of a load
+    constexpr int LB = LA / US;                      // loads in flight of a fragment
+    using Raw = std::conditional_t<BITS == 4 && !B16, u32x2, u32x4>;
 
     round_down_f32();
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -191,14 +196,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
             chan[WHOLE ? 0 : p] = blk0 * FKB * 16 + gq * 4 * FKB + (FKB == 4 && !WHOLE ? (pair0 & 1) * 8 : 0);
         }
     }
-    const int lane_w = gq * a.psw + l16 * 16;
+    const int lane_w = gq * (B16 ? 2 : 1) * a.psw + l16 * 16;
 
     // ---- this wave's steps: [step0, step0 + steps)
     const int step0 = WRES ? 0 : wd_i * jb.steps_per_wave;
     const int steps = WRES ? jb.steps : max(0, min(jb.steps_per_wave, jb.steps - step0));
     const int rounds = (steps + LA - 1) / LA;
 
-    // the step whose operands are loaded next: its tap, and its offsets in the
+    // the step (B16: pair of steps) whose operands are loaded next: its tap, and its offsets in the
     // input and in the image.  (The increments are held in scalar registers:
     // taken from the argument block, the selects below become loads.)
     auto held = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
@@ -206,7 +211,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
               xs_chunk = held(jb.xs_chunk), ws_tap = held(a.tk16), ws_chunk = held(jb.ws_chunk);
     int s_i = 0, tap = 0, left, xs, ws;
     auto first_step = [&] {
-        left = steps;
+        left = steps / US;
         if constexpr (LIN) {
             xs = step0 * CB;
             ws = step0 * ws_chunk;
@@ -226,7 +231,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
     auto next_step = [&] {
         --left;
         if constexpr (LIN) {
-            xs += CB;
+            xs += CB * US;
             ws += left > 0 ? ws_chunk : 0;
         } else {
             // (scalar selects by mask: as conditionals they end up in vector
@@ -243,7 +248,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
     // the taps outside the image (bit 31 always set).  (Lanes whose channels
     // lie past a pixel of fewer than 64 read its first ones: their filters are
     // zero, and no load passes the tensor's end.)
-    const int lane_c = gq * (CB / 4) < a.xpix ? gq * (CB / 4) : 0;
+    const int lane_c = B16 ? gq * 16 : gq * (CB / 4) < a.xpix ? gq * (CB / 4) : 0;
     uint32_t voff[FP], bad[FP];
     auto set_pixels = [&](int mtile) {
         const int m0 = mtile * (FP * 16) + l16;
@@ -292,7 +297,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
     };
 
     v4i A[AS][NF];
-    Raw B[LA][FP];
+    Raw B[LB][FP];
     auto load_b = [&](int u) {
         // (bounds checks see the lane's offset, not the scalar one: 1x1 steps,
         // whose last chunk may pass the tensor's end, add theirs to the lane's;
@@ -302,7 +307,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         for (int tn = 0; tn < FP; ++tn) {
             const uint32_t off = LIN ? voff[tn] + step : ((bad[tn] << step) & 0x80000000u) | voff[tn];
             const int soff = LIN ? 0 : xs;
-            if constexpr (BITS == 4)
+            if constexpr (B16)
+                B[u / 2][tn] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, soff, 0);
+            else if constexpr (BITS == 4)
                 B[u][tn] = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)off, soff, 0);
             else
                 B[u][tn] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)off, soff, 0);
@@ -328,7 +335,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         for (int tn = 0; tn < FP; ++tn) {
             v4i bv;
             if constexpr (BITS == 4) {
-                const uint32_t x0 = B[u][tn][0], x1 = B[u][tn][1];
+                const uint32_t x0 = B[B16 ? u / 2 : u][tn][B16 ? u % 2 * 2 : 0];
+                const uint32_t x1 = B[B16 ? u / 2 : u][tn][B16 ? u % 2 * 2 + 1 : 1];
                 bv = v4i{(int)(x0 & 0x0F0F0F0Fu), (int)((x0 >> 4) & 0x0F0F0F0Fu), (int)(x1 & 0x0F0F0F0Fu),
                          (int)((x1 >> 4) & 0x0F0F0F0Fu)};
             } else {
@@ -382,7 +390,18 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
                 mult[b][i] = (int32_t)__builtin_bit_cast(uint32_t, (float)mult[b][i] * jb.fe.scale);
     };
     // P fragments of run b (its multipliers mu, biases bi) at pixel mbase
-    auto finish = [&](auto &v, int mbase, int cb, const int32_t(&mu)[4 * FE], const int32_t *bi) {
+    constexpr int NWD = 4 * FE * BITS / 32;   // words of a pixel's run
+    auto load_residual = [&](auto &rw, int mbase, int cb) {
+        if constexpr (EXT) {
+            if (de.res && f32) {
+#pragma unroll
+                for (int tn = 0; tn < (int)(sizeof(rw) / sizeof(rw[0])); ++tn)
+                    load_run<BITS, FE>(de, mbase + tn * 16 + l16, cb, rw[tn]);
+            }
+        }
+    };
+    // (the residual's words `rw` are loaded ahead for the f32 form only)
+    auto finish = [&](auto &v, int mbase, int cb, const int32_t(&mu)[4 * FE], const int32_t *bi, const auto &rw) {
         constexpr int P = sizeof(v) / sizeof(v[0]);
         if constexpr (EXT) {
             if (a.mode == QCONV_OUT_REQUANT) {
@@ -398,9 +417,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
 #pragma unroll
             for (int i = 0; i < 4 * FE; ++i) mf[i] = __builtin_bit_cast(float, (uint32_t)mu[i]);
             if (EXT && de.res)
-                epilogue_f32<BITS, P, FE, true>(de, jb.fe, v, mbase, cb, l16, mf);
+                epilogue_f32<BITS, P, FE, true>(de, jb.fe, v, mbase, cb, l16, mf, rw);
             else
-                epilogue_f32<BITS, P, FE, false>(de, jb.fe, v, mbase, cb, l16, mf);
+                epilogue_f32<BITS, P, FE, false>(de, jb.fe, v, mbase, cb, l16, mf, rw);
             return;
         }
         EpiParams<FE> ep;
@@ -415,17 +434,19 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         const int frags = steps * NF;
         for (int i = wave; i < frags; i += a.wt) {
             const int st = i / NF, f = i - st * NF;
-            const int j = (int)fdiv((uint32_t)st, jb.div_taps), tp = st - j * taps;
-            const int off = wpair[NP == 2 ? f >> 1 : 0] + j * 4 * a.psw + tp * ws_tap + (f & 1) * 256;
+            const int j = (int)fdiv((uint32_t)(st / US), jb.div_taps), tp = st / US - j * taps;
+            const int off = wpair[NP == 2 ? f >> 1 : 0] + (j * 4 * US + st % US) * a.psw + tp * ws_tap + (f & 1) * 256;
             dma16(smem + i * 1024, (uint32_t)(lane_w + off), rimg);
         }
         set_pixels(min(mt, a.mtiles - 1));
         first_step();
-#pragma unroll
-        for (int u = 0; u < LA; ++u) {
+        auto fetch = [&](int u) {   // after step u: the loads its registers are free for
+            if (u % US != US - 1) return;
             load_b(u);
             next_step();
-        }
+        };
+#pragma unroll
+        for (int u = 0; u < LA; ++u) fetch(u);
         load_params();
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -443,13 +464,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
                 } else {
                     multiply(u % AS, u, no);
                 }
-                load_b(u);
-                next_step();
+                fetch(u);
             }
         };
         for (; mt < a.mtiles; mt += a.walk) {
             const uint8_t *p = smem + lane * 16;
             read_a(0, p);
+            uint32_t rw[NBK][FP][NWD];
+#pragma unroll
+            for (int b = 0; b < NBK; ++b) load_residual(rw[b], mt * (FP * 16), chan[b]);
             // (the last round's loads are the next tile's first steps)
             if constexpr (MULTI) {
                 round(p, yes, no);
@@ -467,7 +490,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
                 round(p, yes, yes);
             }
 #pragma unroll
-            for (int b = 0; b < NBK; ++b) finish(acc[b], mt * (FP * 16), chan[b], mult[b], bias[EXT ? b : 0]);
+            for (int b = 0; b < NBK; ++b) finish(acc[b], mt * (FP * 16), chan[b], mult[b], bias[EXT ? b : 0], rw[b]);
         }
     } else {
         set_pixels(mt);
@@ -503,8 +526,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         }
         prepare_params();
         if (a.wd == 1) {
+            uint32_t rw[NBK][FP][NWD];
 #pragma unroll
-            for (int b = 0; b < NBK; ++b) finish(acc[b], mt * (FP * 16), chan[b], mult[b], bias[EXT ? b : 0]);
+            for (int b = 0; b < NBK; ++b) load_residual(rw[b], mt * (FP * 16), chan[b]);
+#pragma unroll
+            for (int b = 0; b < NBK; ++b) finish(acc[b], mt * (FP * 16), chan[b], mult[b], bias[EXT ? b : 0], rw[b]);
             return;
         }
         // ---- the waves of a tile add their sums: unit (run b, fragment tn)
@@ -525,6 +551,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         for (int unit = 0; unit < UNITS; ++unit) {
             if (unit % a.wd != wd_i) continue;
             v4i sum[1][FE];
+            uint32_t rw[1][NWD];
+            load_residual(rw, mt * (FP * 16) + (unit % FP) * 16, chan[unit / FP]);
 #pragma unroll
             for (int f = 0; f < FE; ++f) sum[0][f] = acc[unit / FP][unit % FP][f];
             for (int d = 0; d < a.wd; ++d) {
@@ -533,27 +561,29 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
 #pragma unroll
                 for (int f = 0; f < FE; ++f) sum[0][f] += *reinterpret_cast<const v4i *>(p + f * 1024);
             }
-            finish(sum, mt * (FP * 16) + (unit % FP) * 16, chan[unit / FP], mult[unit / FP], bias[EXT ? unit / FP : 0]);
+            finish(sum, mt * (FP * 16) + (unit % FP) * 16, chan[unit / FP], mult[unit / FP], bias[EXT ? unit / FP : 0], rw);
         }
     }
 }
 
-template <int BITS, int FKB, int NP, int FP, bool EXT, int LA, bool MULTI, bool LIN, bool WRES>
+template <int BITS, int FKB, int NP, int FP, bool EXT, int LA, bool MULTI, bool LIN, bool WRES, bool B16>
 static hipError_t launch_direct(const DirectArgs &a, dim3 grid, int threads, size_t lds, hipStream_t stream) {
-    hipLaunchKernelGGL((conv_direct<BITS, FKB, NP, FP, EXT, LA, MULTI, LIN, WRES>), grid, dim3(threads), lds, stream, a);
+    hipLaunchKernelGGL((conv_direct<BITS, FKB, NP, FP, EXT, LA, MULTI, LIN, WRES, B16>), grid, dim3(threads), lds, stream, a);
     return hipGetLastError();
 }
 
-#define QCONV_DIRECT_ONE(B, FKB, NP, FP, E, LA, MU, LIN, WR)                                                      \
-    {B, FKB, NP, FP, E, LA, MU, LIN, WR, &launch_direct<B, FKB, NP, FP, (E != 0), LA, (MU != 0), (LIN != 0), (WR != 0)>, \
-     reinterpret_cast<const void *>(&conv_direct<B, FKB, NP, FP, (E != 0), LA, (MU != 0), (LIN != 0), (WR != 0)>)},
+#define QCONV_DIRECT_ONE(B, FKB, NP, FP, E, LA, MU, LIN, WR, B16)                                                \
+    {B, FKB, NP, FP, E, LA, MU, LIN, WR, B16,                                                                     \
+     &launch_direct<B, FKB, NP, FP, (E != 0), LA, (MU != 0), (LIN != 0), (WR != 0), (B16 != 0)>,                  \
+     reinterpret_cast<const void *>(                                                                              \
+         &conv_direct<B, FKB, NP, FP, (E != 0), LA, (MU != 0), (LIN != 0), (WR != 0), (B16 != 0)>)},
 #define QCONV_DIRECT_EXT(B, FKB, NP, FP, LA, MU, LIN, WR) \
-    QCONV_DIRECT_ONE(B, FKB, NP, FP, 0, LA, MU, LIN, WR) QCONV_DIRECT_ONE(B, FKB, NP, FP, 1, LA, MU, LIN, WR)
-// depth: any filter, then 1x1; resident: 1x1
+    QCONV_DIRECT_ONE(B, FKB, NP, FP, 0, LA, MU, LIN, WR, 0) QCONV_DIRECT_ONE(B, FKB, NP, FP, 1, LA, MU, LIN, WR, 0)
+#define QCONV_DIRECT_B16(FKB, NP, FP, LA, MU, LIN) \
+    QCONV_DIRECT_ONE(4, FKB, NP, FP, 0, LA, MU, LIN, 1, 1) QCONV_DIRECT_ONE(4, FKB, NP, FP, 1, LA, MU, LIN, 1, 1)
+// depth: any filter, then 1x1; resident: 1x1, then any filter
 #define QCONV_DIRECT_SET(B, FKB)                                                              \
-    QCONV_DIRECT_EXT(B, FKB, 1, 1, 9, 0, 0, 0) QCONV_DIRECT_EXT(B, FKB, 1, 2, 9, 0, 0, 0)     \
-    QCONV_DIRECT_EXT(B, FKB, 2, 1, 9, 0, 0, 0) QCONV_DIRECT_EXT(B, FKB, 2, 2, 9, 0, 0, 0)     \
-    QCONV_DIRECT_EXT(B, FKB, 1, 1, 9, 1, 0, 0) QCONV_DIRECT_EXT(B, FKB, 1, 2, 9, 1, 0, 0)     \
+    QCONV_DIRECT_EXT(B, FKB, 1, 1, 9, 0, 0, 0) QCONV_DIRECT_EXT(B, FKB, 1, 1, 9, 1, 0, 0)     \
     QCONV_DIRECT_EXT(B, FKB, 1, 2, 3, 1, 0, 0) QCONV_DIRECT_EXT(B, FKB, 2, 2, 3, 1, 0, 0)     \
     QCONV_DIRECT_EXT(B, FKB, 1, 1, 4, 0, 1, 0) QCONV_DIRECT_EXT(B, FKB, 1, 2, 4, 0, 1, 0)     \
     QCONV_DIRECT_EXT(B, FKB, 1, 1, 8, 0, 1, 0) QCONV_DIRECT_EXT(B, FKB, 1, 2, 8, 0, 1, 0)     \
@@ -561,7 +591,11 @@ static hipError_t launch_direct(const DirectArgs &a, dim3 grid, int threads, siz
     QCONV_DIRECT_EXT(B, FKB, 2, 2, 4, 0, 1, 0) QCONV_DIRECT_EXT(B, FKB, 2, 2, 4, 1, 1, 0)     \
     QCONV_DIRECT_EXT(B, FKB, 2, 4, 4, 0, 1, 0) QCONV_DIRECT_EXT(B, FKB, 2, 4, 4, 1, 1, 0)     \
     QCONV_DIRECT_EXT(B, FKB, 2, 2, 1, 0, 1, 1) QCONV_DIRECT_EXT(B, FKB, 2, 2, 2, 0, 1, 1)     \
+    QCONV_DIRECT_EXT(B, FKB, 2, 4, 1, 0, 1, 1) QCONV_DIRECT_EXT(B, FKB, 2, 4, 2, 0, 1, 1)     \
     QCONV_DIRECT_EXT(B, FKB, 2, 2, 4, 0, 1, 1) QCONV_DIRECT_EXT(B, FKB, 2, 2, 4, 1, 1, 1)     \
     QCONV_DIRECT_EXT(B, FKB, 2, 2, 3, 1, 0, 1)
+#define QCONV_DIRECT_SET16(FKB)                                                               \
+    QCONV_DIRECT_B16(FKB, 2, 2, 2, 0, 1) QCONV_DIRECT_B16(FKB, 2, 4, 2, 0, 1)                 \
+    QCONV_DIRECT_B16(FKB, 2, 2, 4, 0, 1) QCONV_DIRECT_B16(FKB, 2, 2, 4, 1, 1)
 
 }  // namespace qconv

@@ -4,7 +4,7 @@
 
 namespace qconv {
 
-DirectInstance g_direct_b4f2[] = {QCONV_DIRECT_SET(4, 2)};
+DirectInstance g_direct_b4f2[] = {QCONV_DIRECT_SET(4, 2) QCONV_DIRECT_SET16(2)};
 int g_direct_b4f2_count = (int)(sizeof(g_direct_b4f2) / sizeof(g_direct_b4f2[0]));
 
 }  // namespace qconv

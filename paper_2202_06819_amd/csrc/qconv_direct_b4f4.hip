@@ -4,7 +4,7 @@
 
 namespace qconv {
 
-DirectInstance g_direct_b4f4[] = {QCONV_DIRECT_SET(4, 4)};
+DirectInstance g_direct_b4f4[] = {QCONV_DIRECT_SET(4, 4) QCONV_DIRECT_SET16(4)};
 int g_direct_b4f4_count = (int)(sizeof(g_direct_b4f4) / sizeof(g_direct_b4f4[0]));
 
 }  // namespace qconv

@@ -747,11 +747,17 @@ bool direct_lin(const qconv_desc *d) {
     return d->r == 1 && d->s == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 && d->pad_w == 0;
 }
 
+// A load covers two steps: 4-bit resident 1x1 kernels, wherever the channels are
+// whole pairs of steps.
+bool direct_two_steps(const qconv_desc *d, const DirectChoice &c) {
+    return c.resident && direct_lin(d) && d->bits == 4 && d->c % 128 == 0 && c.la % 2 == 0;
+}
+
 // ---- when a prepared layer runs on the direct kernels.  A launch time is
 // estimated for the wide tile's plan and for each wave tile below as a sum of
 // terms (us) in what the launch does, and the direct kernels take the layer
 // where their best estimate is clearly lower.  The coefficients are least-squares
-// fits to about 1,080 random layers (1x1 to 5x5, strides 1 and 2, 16 to 2048
+// fits to about 1,210 random layers (1x1 to 5x5, strides 1 and 2, 16 to 2048
 // channels, 7 to 112 pixels a side, batch 1 to 256, both widths), each timed
 // with every wave tile and with the wide tile a caller would take; the
 // estimates' errors are 12-17 %.  What they say: a wide launch pays 0.5-0.75 us
@@ -759,40 +765,47 @@ bool direct_lin(const qconv_desc *d) {
 // step of its waves, but loads every operand of every step through the L1, so
 // that few stages and much work favour the wide kernels.
 struct DirectCandidate {
-    int lin;
+    int lin, two;
     DirectChoice c;
     float us[8];
 };
 constexpr DirectCandidate kDirectCandidates[] = {
-    // lin np fp wd wt la resident   us: base, round, step, traffic / round x waves, MFMA, MB, filter MB, epilogue
-    {0, {1, 1, 1, 1, 9, 0}, {2.74f, 0.0f, 0.0569f, 0.0204f, 0.0682f, 0.0652f, 0.0f, 0.0f}},
-    {0, {1, 1, 2, 1, 9, 0}, {2.89f, 0.0f, 0.0713f, 0.00606f, 0.0997f, 0.12f, 0.0422f, 0.0f}},
-    {0, {1, 1, 4, 1, 9, 0}, {2.55f, 0.0f, 0.132f, 0.0206f, 0.0583f, 0.139f, 0.219f, 0.0f}},
-    {0, {1, 1, 8, 1, 9, 0}, {1.63f, 0.0f, 0.309f, 0.00792f, 0.101f, 0.214f, 0.303f, 0.0f}},
-    {0, {1, 2, 1, 1, 3, 0}, {3.04f, 0.0f, 0.0867f, 0.0114f, 0.0618f, 0.0987f, 0.0f, 0.0f}},
-    {0, {1, 2, 4, 1, 3, 0}, {2.94f, 0.0f, 0.227f, 0.0487f, 0.00889f, 0.114f, 0.0f, 0.0207f}},
-    {0, {2, 2, 1, 1, 3, 0}, {3.42f, 0.0f, 0.122f, 0.0103f, 0.0331f, 0.0435f, 0.0f, 0.0911f}},
-    {0, {2, 2, 2, 1, 3, 0}, {3.83f, 0.0f, 0.14f, 0.0104f, 0.0428f, 0.0804f, 0.0f, 0.102f}},
-    {0, {2, 2, 4, 1, 3, 0}, {3.24f, 0.0f, 0.27f, 0.0218f, 0.0276f, 0.0754f, 0.0f, 0.205f}},
-    {0, {2, 2, 1, 4, 3, 1}, {4.32f, 0.0f, 0.105f, 0.0899f, 0.0f, 0.0704f, 1.56f, 0.0f}},
-    {0, {2, 2, 1, 8, 3, 1}, {4.62f, 0.0f, 0.272f, 0.0f, 0.0f, 0.109f, 0.429f, 0.0f}},
-    {1, {1, 1, 1, 1, 4, 0}, {0.0f, 0.0f, 0.698f, 0.0256f, 0.0657f, 0.096f, 1.13f, 0.0f}},
-    {1, {1, 1, 1, 1, 8, 0}, {2.46f, 0.0f, 0.0533f, 0.0055f, 0.1f, 0.102f, 0.305f, 0.0f}},
-    {1, {1, 1, 2, 1, 8, 0}, {2.58f, 0.0f, 0.0789f, 0.00597f, 0.0878f, 0.169f, 0.46f, 0.0f}},
-    {1, {1, 1, 4, 1, 8, 0}, {0.0f, 0.0f, 0.437f, 0.00324f, 0.0951f, 0.233f, 0.497f, 0.0f}},
-    {1, {1, 2, 1, 1, 4, 0}, {0.0f, 0.0f, 0.728f, 0.0178f, 0.0626f, 0.0878f, 1.0f, 0.0f}},
-    {1, {1, 2, 1, 1, 8, 0}, {2.57f, 0.0f, 0.0711f, 0.00888f, 0.0629f, 0.118f, 0.519f, 0.0f}},
-    {1, {2, 2, 1, 1, 4, 0}, {3.09f, 0.0f, 0.0876f, 0.0531f, 0.0f, 0.046f, 0.112f, 0.0f}},
-    {1, {2, 2, 2, 1, 4, 0}, {3.59f, 0.0f, 0.121f, 0.052f, 0.00376f, 0.0425f, 0.108f, 0.0f}},
-    {1, {2, 4, 1, 1, 4, 0}, {3.41f, 0.0f, 0.156f, 0.0409f, 0.0236f, 0.0541f, 0.116f, 0.00547f}},
-    {1, {2, 2, 1, 4, 1, 1}, {3.12f, 0.0f, 0.0f, 0.147f, 0.0f, 0.181f, 10.1f, 0.0f}},
-    {1, {2, 2, 1, 4, 2, 1}, {3.13f, 0.0f, 0.098f, 0.0771f, 0.0f, 0.168f, 4.49f, 0.0f}},
-    {1, {2, 2, 1, 4, 4, 1}, {3.01f, 0.0f, 0.213f, 0.0445f, 0.0f, 0.0871f, 3.24f, 0.0f}},
+    // lin, two steps a load (-1: either), {np fp wd wt la resident},
+    // us: base, round, step, traffic (resident: step x waves), MFMA (round x waves), MB, filter MB, epilogue
+    {0, -1, {1, 1, 1, 1, 9, 0}, {2.74f, 0.0f, 0.0585f, 0.0229f, 0.0636f, 0.0593f, 0.0f, 0.0f}},
+    {0, -1, {1, 1, 2, 1, 9, 0}, {2.91f, 0.0f, 0.0693f, 0.0114f, 0.088f, 0.114f, 0.0437f, 0.0f}},
+    {0, -1, {1, 1, 4, 1, 9, 0}, {2.6f, 0.0f, 0.129f, 0.0251f, 0.0492f, 0.137f, 0.218f, 0.0f}},
+    {0, -1, {1, 1, 8, 1, 9, 0}, {2.0f, 0.0f, 0.267f, 0.0106f, 0.0956f, 0.208f, 0.355f, 0.0f}},
+    {0, -1, {1, 2, 1, 1, 3, 0}, {3.03f, 0.0f, 0.0864f, 0.0126f, 0.0615f, 0.092f, 0.0f, 0.0f}},
+    {0, -1, {1, 2, 4, 1, 3, 0}, {2.89f, 0.0f, 0.234f, 0.0428f, 0.0219f, 0.159f, 0.0f, 0.0f}},
+    {0, -1, {2, 2, 1, 1, 3, 0}, {3.45f, 0.0f, 0.121f, 0.0133f, 0.0333f, 0.0483f, 0.0f, 0.0296f}},
+    {0, -1, {2, 2, 2, 1, 3, 0}, {3.9f, 0.0f, 0.135f, 0.00906f, 0.0501f, 0.0988f, 0.0f, 0.0112f}},
+    {0, -1, {2, 2, 4, 1, 3, 0}, {3.43f, 0.0f, 0.248f, 0.0196f, 0.0408f, 0.0583f, 0.0f, 0.0f}},
+    {0, -1, {2, 2, 1, 4, 3, 1}, {4.26f, 0.0f, 0.11f, 0.0881f, 0.0f, 0.0515f, 1.81f, 0.0f}},
+    {0, -1, {2, 2, 1, 8, 3, 1}, {4.54f, 0.0f, 0.275f, 0.0f, 0.0f, 0.102f, 0.804f, 0.0f}},
+    {1, -1, {1, 1, 1, 1, 4, 0}, {0.0f, 0.0f, 0.712f, 0.0125f, 0.0997f, 0.0982f, 1.22f, 0.0f}},
+    {1, -1, {1, 1, 1, 1, 8, 0}, {2.54f, 0.0f, 0.0454f, 0.00582f, 0.0977f, 0.12f, 0.459f, 0.0f}},
+    {1, -1, {1, 1, 2, 1, 8, 0}, {2.48f, 0.0f, 0.0858f, 0.00906f, 0.081f, 0.145f, 0.429f, 0.0f}},
+    {1, -1, {1, 1, 4, 1, 8, 0}, {0.0f, 0.0f, 0.435f, 0.0f, 0.104f, 0.161f, 0.666f, 0.0f}},
+    {1, -1, {1, 2, 1, 1, 4, 0}, {0.0f, 0.0f, 0.734f, 0.00902f, 0.0758f, 0.0963f, 1.71f, 0.0f}},
+    {1, -1, {1, 2, 1, 1, 8, 0}, {2.62f, 0.0f, 0.0686f, 0.00693f, 0.0648f, 0.124f, 0.444f, 0.0f}},
+    {1, -1, {2, 2, 1, 1, 4, 0}, {3.1f, 0.0f, 0.0889f, 0.0538f, 0.0f, 0.0426f, 0.00232f, 0.0f}},
+    {1, -1, {2, 2, 2, 1, 4, 0}, {3.56f, 0.0f, 0.122f, 0.0516f, 0.0f, 0.0789f, 0.203f, 0.0f}},
+    {1, -1, {2, 4, 1, 1, 4, 0}, {3.42f, 0.0f, 0.161f, 0.0419f, 0.022f, 0.0381f, 0.0101f, 0.0194f}},
+    {1, -1, {2, 2, 1, 4, 1, 1}, {3.19f, 0.0f, 0.0f, 0.165f, 0.0f, 0.191f, 6.42f, 0.0f}},
+    {1, -1, {2, 4, 1, 8, 1, 1}, {3.58f, 0.64f, 0.0f, 0.0f, 0.0f, 0.2f, 23.8f, 0.0f}},
+    {1, 0, {2, 2, 1, 4, 2, 1}, {3.28f, 0.0f, 0.0f, 0.0993f, 0.0f, 0.202f, 2.89f, 0.0f}},
+    {1, 0, {2, 4, 1, 4, 2, 1}, {3.88f, 0.0f, 0.0f, 0.115f, 0.0f, 0.241f, 3.4f, 0.0f}},
+    {1, 1, {2, 2, 1, 4, 2, 1}, {2.19f, 0.0f, 0.664f, 0.0f, 0.0f, 0.0f, 7.57f, 0.0f}},
+    {1, 1, {2, 4, 1, 4, 2, 1}, {3.09f, 0.0f, 0.19f, 0.31f, 0.0f, 0.0f, 9.07f, 0.0f}},
+    {1, 0, {2, 2, 1, 4, 4, 1}, {2.85f, 0.0f, 0.222f, 0.0334f, 0.0f, 0.128f, 2.74f, 0.0f}},
+    {1, 1, {2, 2, 1, 4, 4, 1}, {3.44f, 0.0f, 0.11f, 0.0779f, 0.0567f, 0.0177f, 1.44f, 0.0f}},
+    {1, 1, {2, 2, 1, 8, 4, 1}, {3.77f, 0.0f, 0.279f, 0.0f, 0.0f, 0.0173f, 1.69f, 0.0f}},
 };
 // us of a wide launch: base, stage, MFMA, band, epilogue, MB, filter MB, any-size filter, split, shared SIMD, MFMA of one wave
 constexpr float kWideCost[2][11] = {
-    {2.92f, 0.753f, 0.0059f, 0.222f, 0.0669f, 0.0f, 0.238f, 0.0133f, 2.08f, 0.0192f, 0.00426f},
-    {2.93f, 0.512f, 0.011f, 0.186f, 0.0582f, 0.0471f, 0.173f, 0.0f, 3.49f, 0.029f, 0.00407f},
+    {2.91f, 0.769f, 0.0052f, 0.195f, 0.0713f, 0.0f, 0.247f, 0.00736f, 2.11f, 0.0254f, 0.00517f},
+    {2.83f, 0.513f, 0.00896f, 0.194f, 0.0564f, 0.0521f, 0.0753f, 0.0f, 3.35f, 0.0288f, 0.00898f},
 };
 // (end of the fitted costs)
 
@@ -865,6 +878,7 @@ DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, con
     double best_us = 1e30;
     for (const DirectCandidate &k : kDirectCandidates) {
         if (k.lin != lin || (proj && k.c.resident) || k.c.wd > z.steps) continue;
+        if (k.two >= 0 && (k.two != 0) != direct_two_steps(d, k.c)) continue;
         // some are compiled for one round of their steps in flight, some for several only
         const int64_t wave_steps = (z.steps + k.c.wd - 1) / k.c.wd;
         if (lin && wave_steps > k.c.la && (k.c.la < 4 || (k.c.la == 4 && k.c.np == 1))) continue;
@@ -924,7 +938,9 @@ bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_t
     const bool lin = direct_lin(d);
     if (!lin && d->c % 64 != 0 && d->c > 64) return false;
     const int64_t steps = taps * ((d->c + 63) / 64), wave_steps = (steps + c.wd - 1) / c.wd;
-    out.inst = direct_instance(d->bits, t.frag_k, c.np, c.fp, ext, c.la, wave_steps > c.la, lin, c.resident);
+    // (two steps a load wherever the channels are whole pairs of steps)
+    const bool two = direct_two_steps(d, c);
+    out.inst = direct_instance(d->bits, t.frag_k, c.np, c.fp, ext, c.la, wave_steps > c.la, lin, c.resident, two);
     if (!out.inst) return false;
     memset(&a, 0, sizeof(a));
     a.w = static_cast<const uint8_t *>(w);

@@ -196,9 +196,10 @@ struct TileEntry {
 };
 
 // A direct convolution kernel: image fragments per block, 32-channel pairs and
-// 16-pixel fragments per wave, steps in flight, filters resident in LDS.
+// 16-pixel fragments per wave, steps in flight, filters resident in LDS, two
+// steps a load.
 struct DirectInstance {
-    int bits, fkb, np, fp, ext, la, multi, lin, resident;
+    int bits, fkb, np, fp, ext, la, multi, lin, resident, two_steps;
     hipError_t (*launch)(const DirectArgs &, dim3 grid, int threads, size_t lds_bytes, hipStream_t);
     const void *kernel;
 };
@@ -230,7 +231,7 @@ const AblationInstance *ablation_instance(const char *tile_name, int mask);
 const ProjInstance *proj_instance(const char *tile_name);
 
 // Defined in qconv_direct.hip.
-const DirectInstance *direct_instance(int bits, int fkb, int np, int fp, int ext, int la, int multi, int lin, int resident);
+const DirectInstance *direct_instance(int bits, int fkb, int np, int fp, int ext, int la, int multi, int lin, int resident, int two_steps);
 
 // Defined in qconv_pack.hip.
 hipError_t launch_pack(const int8_t *src, void *dst, int32_t n, int32_t c, int32_t h, int32_t w, int32_t bits,
