@@ -12,7 +12,6 @@
 #include <initializer_list>
 #include <map>
 #include <mutex>
-#include <string>
 #include <tuple>
 #include <set>
 #include <unordered_map>
@@ -186,15 +185,28 @@ int64_t vrow_of(const qconv_desc *d, int64_t p, int64_t q, int64_t m) {
     return img * (d->h + 2 * d->pad_h) + (rem / q) * d->stride_h;
 }
 
+// Key of the host's shape caches: a descriptor's fields, and what else a cached
+// value depends on; unused entries are zero.
+struct ShapeKey {
+    int32_t v[16] = {};
+    bool operator==(const ShapeKey &o) const { return memcmp(v, o.v, sizeof(v)) == 0; }
+};
+struct ShapeKeyHash {
+    size_t operator()(const ShapeKey &k) const {
+        uint64_t h = 1469598103934665603ull;   // FNV-1a over the words
+        for (int32_t x : k.v) h = (h ^ (uint32_t)x) * 1099511628211ull;
+        return (size_t)(h ^ (h >> 32));
+    }
+};
+
 // Largest number of padded rows any workgroup of tile_p pixels touches.
 int64_t band_rows(const qconv_desc *d, int64_t p, int64_t q, int64_t tile_p) {
     static std::mutex mu;
-    static std::unordered_map<std::string, int64_t> cache;
+    static std::unordered_map<ShapeKey, int64_t, ShapeKeyHash> cache;
     // keyed by everything the result depends on: the output extent (p, q)
     // follows from both axes' strides and paddings
-    char key[192];
-    snprintf(key, sizeof(key), "%d,%d,%d,%d,%d,%d,%d,%d,%d,%lld,%lld,%lld", d->n, d->h, d->w, d->r, d->s, d->stride_h,
-             d->stride_w, d->pad_h, d->pad_w, (long long)p, (long long)q, (long long)tile_p);
+    const ShapeKey key{{d->n, d->h, d->w, d->r, d->s, d->stride_h, d->stride_w, d->pad_h, d->pad_w, (int32_t)p,
+                        (int32_t)q, (int32_t)tile_p}};
     {
         std::lock_guard<std::mutex> g(mu);
         auto it = cache.find(key);
@@ -364,7 +376,7 @@ int plan_tile(const qconv_desc *d, const qconv_layout_info &li, const qconv_tile
     return QCONV_OK;
 }
 
-int pick_default(const qconv_desc *d, const qconv_layout_info &li) {
+int score_default(const qconv_desc *d, const qconv_layout_info &li) {
     // Static heuristic: favour 64x64 wave tiles (operand reuse), the pipelined
     // kernel where it applies, and enough workgroups to cover every CU; the
     // sweep harness measures the alternatives.
@@ -390,6 +402,25 @@ int pick_default(const qconv_desc *d, const qconv_layout_info &li) {
             best = i;
         }
     }
+    return best;
+}
+
+// score_default's answer for a (kernel) descriptor, kept: scoring plans every
+// compiled tile, 38 us a call, more than the kernels of a small layer take.
+int pick_default(const qconv_desc *d, const qconv_layout_info &li) {
+    static std::mutex mu;
+    static std::unordered_map<ShapeKey, int, ShapeKeyHash> cache;
+    const ShapeKey key{{d->n, d->h, d->w, d->c, d->k, d->r, d->s, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->bits,
+                        d->x_signed, d->w_signed, d->nb}};
+    {
+        std::lock_guard<std::mutex> g(mu);
+        auto it = cache.find(key);
+        if (it != cache.end()) return it->second;
+    }
+    const int best = score_default(d, li);
+    std::lock_guard<std::mutex> g(mu);
+    if (cache.size() > 4096) cache.clear();
+    cache[key] = best;
     return best;
 }
 

@@ -15,6 +15,7 @@ Tensor conventions
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 import threading
 
@@ -152,17 +153,21 @@ def _check(rc: int, what: str) -> int:
     return rc
 
 
+_desc_values = operator.itemgetter(*(f for f, _ in QConvDesc._fields_ if f != "nb"))   # nb, the last field, may be missing
+_layout_fields = tuple(f for f, _ in QConvLayoutInfo._fields_)
+
+
 def make_desc(d: dict | QConvDesc) -> QConvDesc:
     if isinstance(d, QConvDesc):
         return d
-    return QConvDesc(**{f: int(d.get(f, 0) if f == "nb" else d[f]) for f, _ in QConvDesc._fields_})
+    return QConvDesc(*map(int, _desc_values(d)), int(d.get("nb", 0)))
 
 
 def layout(d: dict) -> dict:
     """Output extent and buffer sizes of a descriptor (host only)."""
     info = QConvLayoutInfo()
     _check(lib().qconv_layout(ctypes.byref(make_desc(d)), ctypes.byref(info)), "qconv_layout")
-    return {f: getattr(info, f) for f, _ in QConvLayoutInfo._fields_}
+    return {f: getattr(info, f) for f in _layout_fields}
 
 
 def tiles() -> list[dict]:
@@ -446,7 +451,7 @@ def conv2d(d: dict, x: torch.Tensor, w: torch.Tensor, *, requant: bool = False, 
     split-K uses the library's device scratch instead of `workspace`).
     """
     desc = make_desc(d)
-    info = layout(d)
+    info = layout(desc)
     bits = desc.bits
     if out is None:
         if requant:
@@ -469,14 +474,14 @@ def conv2d(d: dict, x: torch.Tensor, w: torch.Tensor, *, requant: bool = False, 
     if noalloc:
         if not prepared or workspace is not None:
             raise QConvError(EINVAL, "noalloc runs prepared filters and takes no workspace")
-        wb = prepared_filter_bytes(d, tile)
+        wb = prepared_filter_bytes(desc, tile)
         rc = lib().qconv2d_prepared_noalloc(ctypes.byref(desc), _dev_ptr(x, "x", info["x_bytes"]),
                                             _dev_ptr(w, "w", wb), w.numel() * w.element_size(), ctypes.byref(epi),
                                             _dev_ptr(out, "y", y_bytes), int(tile), int(splits), _vp(_stream(stream)))
         _check(rc, "qconv2d_prepared_noalloc")
         return out
     if prepared:
-        wb = prepared_filter_bytes(d, tile)
+        wb = prepared_filter_bytes(desc, tile)
         rc = lib().qconv2d_prepared(ctypes.byref(desc), _dev_ptr(x, "x", info["x_bytes"]), _dev_ptr(w, "w", wb),
                                     w.numel() * w.element_size(), ctypes.byref(epi), _dev_ptr(out, "y", y_bytes),
                                     int(tile), int(splits), ws_ptr, ws_bytes, _vp(_stream(stream)))
