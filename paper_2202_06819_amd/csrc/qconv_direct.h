@@ -329,6 +329,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
     };
 
     v4i acc[NBK][FP][FE];
+    // (a resident kernel of one round starts from the biases; in those of several
+    // the registers cost more than the additions: 79 -> 85 us for two 7x7 bottleneck
+    // blocks)
+    constexpr bool BIAS0 = EXT && WRES && !MULTI;
+    v4i sum0[BIAS0 ? NF : 1];
     // (the first step of a tile starts the sums: no clearing)
     auto multiply = [&](int aset, int u, auto start) {
 #pragma unroll
@@ -345,7 +350,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
 #pragma unroll
             for (int f = 0; f < NF; ++f)
                 acc[f / FE][tn][f % FE] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
-                    A[aset][f], bv, decltype(start)::value ? v4i{0, 0, 0, 0} : acc[f / FE][tn][f % FE], 0, 0, 0);
+                    A[aset][f], bv,
+                    !decltype(start)::value ? acc[f / FE][tn][f % FE] : BIAS0 ? sum0[f] : v4i{0, 0, 0, 0}, 0, 0, 0);
         }
     };
     constexpr std::true_type yes{};
@@ -403,7 +409,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
     // (the residual's words `rw` are loaded ahead for the f32 form only)
     auto finish = [&](auto &v, int mbase, int cb, const int32_t(&mu)[4 * FE], const int32_t *bi, const auto &rw) {
         constexpr int P = sizeof(v) / sizeof(v[0]);
-        if constexpr (EXT) {
+        if constexpr (EXT && !BIAS0) {
             if (a.mode == QCONV_OUT_REQUANT) {
 #pragma unroll
                 for (int tn = 0; tn < P; ++tn)
@@ -451,6 +457,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         prepare_params();
+        if constexpr (BIAS0) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    sum0[f][i] = a.mode == QCONV_OUT_REQUANT
+                                     ? (int)((uint32_t)bias[f / FE][4 * (f % FE) + i] << (uint32_t)a.acc_shift) : 0;
+        }
         // one round: LA steps, each loading its set again for the round after
         auto round = [&](const uint8_t *p, auto first, auto last) {
 #pragma unroll

@@ -244,6 +244,9 @@ struct UnrollArgs {
     int32_t taps_h, stride_h, pad_h, out_h;
     int32_t taps_w, stride_w, pad_w, wout;
     int32_t c_out, lw;
+    // unroll_runs (filled in by launch_unroll)
+    FastDiv div_out_h, div_vpp, div_run;
+    int32_t pixels_per_round;
 };
 
 // Defined in qconv_unroll.hip.
