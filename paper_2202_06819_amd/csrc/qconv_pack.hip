@@ -23,10 +23,8 @@
 
 namespace qconv {
 
-constexpr int PK_C = 64;          // channels per tile
 constexpr int PK_P = 64;          // pixels per tile (64-byte segments of each channel row)
 constexpr int PK_PITCH = 68;      // LDS row pitch in bytes (17 dwords: conflict-free column reads)
-constexpr int PK_THREADS = 128;   // phase 2: 8 channel groups x 16 pixel quads
 
 // Same renumbering as the convolution kernels: block b runs on XCD b % 8;
 // give every XCD a contiguous range so neighbouring pixel tiles (which share
@@ -44,8 +42,10 @@ __device__ __forceinline__ uint32_t gather_byte(const uint32_t (&t)[4], int j) {
 }
 
 // (ptiles, ctiles, nb: the divisors of the block and image decompositions)
-template <int BITS, bool SIGNED>
-__global__ void __launch_bounds__(PK_THREADS)
+// PK_C: channels per tile, 2 PK_C threads (phase 2: PK_C / 8 channel groups x 16
+// pixel quads)
+template <int BITS, bool SIGNED, int PK_C>
+__global__ void __launch_bounds__(2 * PK_C)
     pack_nchw(const int8_t *__restrict__ src, const int8_t *end, uint8_t *__restrict__ dst, int c, int hw,
               FastDiv ptiles, FastDiv ctiles, FastDiv nb) {
     constexpr int LO = SIGNED ? -(1 << (BITS - 1)) : 0;
@@ -121,8 +121,8 @@ __global__ void __launch_bounds__(PK_THREADS)
     // ---- phase 2: a lane takes 8 channels (group g) x 4 pixels (quad q):
     // 8 dword reads, an in-register transpose, and one output word (4-bit) or
     // two (8-bit) per pixel
-    const int g = tid & 7;
-    const int q = tid >> 3;
+    const int g = tid % (PK_C / 8);
+    const int q = tid / (PK_C / 8);
     const int cg = c0 + 8 * g;
     if (cg >= c) return;
     uint32_t d[8];
@@ -157,19 +157,30 @@ hipError_t launch_pack(const int8_t *src, void *dst, int32_t n, int32_t c, int32
                        int32_t is_signed, int32_t nb, hipStream_t stream) {
     const int hw = h * w;
     const int ptiles = (hw + PK_P - 1) / PK_P;
-    const int ctiles = (c + PK_C - 1) / PK_C;
+    const int pkc = c > 64 ? 128 : 64;
+    const int ctiles = (c + pkc - 1) / pkc;
     const long long blocks = (long long)n * ptiles * ctiles;
     uint8_t *d = static_cast<uint8_t *>(dst);
     const int8_t *end = src + (size_t)n * c * hw;
-    const dim3 grid((unsigned)blocks), block(PK_THREADS);
+    const dim3 grid((unsigned)blocks), block(2 * pkc);
     const FastDiv dp = make_fastdiv((uint32_t)ptiles), dc = make_fastdiv((uint32_t)ctiles),
                   dn = make_fastdiv((uint32_t)(nb > 0 ? nb : 1));
-    if (bits == 4 && is_signed)
-        hipLaunchKernelGGL((pack_nchw<4, true>), grid, block, 0, stream, src, end, d, c, hw, dp, dc, dn);
-    else if (bits == 4)
-        hipLaunchKernelGGL((pack_nchw<4, false>), grid, block, 0, stream, src, end, d, c, hw, dp, dc, dn);
-    else
-        hipLaunchKernelGGL((pack_nchw<8, true>), grid, block, 0, stream, src, end, d, c, hw, dp, dc, dn);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, src, end, d, c, hw, dp, dc, dn); };
+    if (pkc == 128) {
+        if (bits == 4 && is_signed)
+            go(pack_nchw<4, true, 128>);
+        else if (bits == 4)
+            go(pack_nchw<4, false, 128>);
+        else
+            go(pack_nchw<8, true, 128>);
+    } else {
+        if (bits == 4 && is_signed)
+            go(pack_nchw<4, true, 64>);
+        else if (bits == 4)
+            go(pack_nchw<4, false, 64>);
+        else
+            go(pack_nchw<8, true, 64>);
+    }
     return hipGetLastError();
 }
 
