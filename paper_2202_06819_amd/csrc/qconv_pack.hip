@@ -3,19 +3,22 @@
 // axis; Sec. 3.3: channels innermost so consumers read it coalesced).
 //
 // The operation is a transpose of each image's C x (H*W) plane.  A workgroup
-// of 128 threads owns a tile of 64 channels x 64 pixels (small tiles, so even
-// a batch-8 56x56 tensor spreads over more than twice as many workgroups as
-// there are CUs).  It reads the tile row by row (each channel's pixels are
-// contiguous in NCHW: 32 bytes per lane, two lanes per 64-byte row segment),
-// saturates every value into the target range and parks it in LDS; it then
-// reads 8 channels x 4 pixels per lane as dwords, transposes the bytes in
-// registers, packs nibbles and writes each pixel's words.  The LDS row pitch
-// of 17 dwords keeps the column reads of a wave (8 channel groups x 8 pixel
-// quads) free of bank conflicts.  The kernel is HBM-bound: every input byte
-// is read once and every output byte written once.  Rows of any length are read
-// with 16-byte loads, unaligned where the row is: a 41x768x59x62 tensor (rows of
-// 3658 bytes) takes 32.7 us (5.3 TB/s) against 236 us with byte loads there, the
-// rate of aligned rows (64x256x56x56: 13.7 us, 5.6 TB/s).
+// owns a tile of PK_C channels x 64 pixels, with two threads per channel.  It
+// reads the tile row by row (each channel's pixels are contiguous in NCHW: 32
+// bytes per lane, two lanes per 64-byte row segment), saturates every value into
+// the target range and parks it in LDS; it then reads 8 channels x 4 pixels per
+// lane as dwords, transposes the bytes in registers, packs nibbles and writes
+// each pixel's words.  The LDS row pitch is 17 dwords, odd, so that the channels
+// of a column lie in different banks.
+//
+// The kernel is HBM-bound: every input byte is read once and every output byte
+// written once.  Up to 64 channels PK_C is 64, which wastes no rows and gives a
+// batch-8 56x56 tensor more than twice as many workgroups as there are CUs.
+// Above 64 channels it is 128: a pixel's packed words are then written in 64-byte
+// runs (4-bit) instead of 32-byte ones, 41x768x59x62 29.5 us (5.9 TB/s) against
+// 32.7 us in 64-channel tiles, 64x256x56x56 13.6 against 13.8 us.  Rows of any
+// length are read with 16-byte loads, unaligned where the row is: those rows of
+// 3658 bytes took 236 us with byte loads.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
