@@ -546,6 +546,19 @@ int qconv_probe_mfma_i8_shape(int32_t shape, int32_t blocks, int32_t iters, int3
 int qconv_last_launch(int64_t *grid, int64_t *threads, int64_t *lds_bytes);
 
 /*
+ * qconv_last_kernel -- host only: the kernel that launch ran ("" when the
+ * thread has launched none), in a buffer of the calling thread that its next
+ * convolution call overwrites.  A tile's name (qconv_tile_info.name) for the
+ * staged and wide kernels, else a direct kernel's:
+ *   direct_b<bits>_k<frag_k of the filter image>_f<16-pixel fragments>x<32-channel
+ *   pairs per wave>_d<waves sharing a tile's depth>_t<tiles per workgroup>_l<steps
+ *   in flight>_depth|resident, then _1x1 (a 1x1 filter at stride 1), _two (two
+ *   steps a load), _rounds (several rounds of the steps in flight), _ext (the
+ *   bias and residual epilogue).
+ */
+const char *qconv_last_kernel(void);
+
+/*
  * qconv_probe_launch -- measurement aid, not part of the convolution: an
  * empty kernel over `blocks` workgroups of `threads` threads with `lds_bytes`
  * of dynamic LDS.  Its time per launch (back to back, or replayed from a

@@ -33,7 +33,7 @@ namespace {
 
 thread_local char g_err[256] = "";
 
-// Geometry of the calling thread's most recent convolution launch.
+// Geometry and kernel of the calling thread's most recent convolution launch.
 struct LaunchGeometry {
     int64_t grid = 0, threads = 0, lds = 0;
     char kernel[96] = "";
@@ -928,6 +928,13 @@ DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, con
     return best && best_us * margin < wide_estimate(d, t, pl, z, lin) ? best->c : none;
 }
 
+// The name of a direct launch, as qconv_last_kernel documents it.
+void name_direct(const DirectChoice &c, const DirectInstance &i, char *out, size_t size) {
+    snprintf(out, size, "direct_b%d_k%d_f%dx%d_d%d_t%d_l%d_%s%s%s%s%s", i.bits, i.fkb, c.fp, c.np, c.wd, c.wt, c.la,
+             c.resident ? "resident" : "depth", i.lin ? "_1x1" : "", i.two_steps ? "_two" : "", i.multi ? "_rounds" : "",
+             i.ext ? "_ext" : "");
+}
+
 // One job of a direct launch (its epilogue comes later): filter r x s with
 // padding (ph, pw), the first tap `tap0` of the image.
 void direct_job(const qconv_desc *d, const qconv_layout_info &li, const DirectArgs &a, DirectJob &j, const void *x,
@@ -1260,7 +1267,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
             g_last_launch.grid = dl.grid;
             g_last_launch.threads = dl.threads;
             g_last_launch.lds = dl.lds;
-            snprintf(g_last_launch.kernel, sizeof(g_last_launch.kernel), "%s", te.info.name);
+            name_direct(dc, *dl.inst, g_last_launch.kernel, sizeof(g_last_launch.kernel));
             return QCONV_OK;
         }
     }
@@ -1652,6 +1659,8 @@ int qconv_last_launch(int64_t *grid, int64_t *threads, int64_t *lds_bytes) {
     if (lds_bytes) *lds_bytes = g_last_launch.lds;
     return g_last_launch.grid > 0 ? QCONV_OK : fail(QCONV_EINVAL, "no convolution launched on this thread yet");
 }
+
+const char *qconv_last_kernel(void) { return g_last_launch.kernel; }
 
 int qconv_probe_launch(int32_t blocks, int32_t threads, int32_t lds_bytes, void *stream) {
     g_err[0] = 0;

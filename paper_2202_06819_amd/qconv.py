@@ -126,6 +126,8 @@ def lib() -> ctypes.CDLL:
         L.qconv_probe_launch.argtypes = [_i32, _i32, _i32, _vp]
         L.qconv_probe_grid_meet.argtypes = [_i32, _i32, _i32, _vp, _vp, _vp]
         L.qconv_last_launch.argtypes = [P(_i64), P(_i64), P(_i64)]
+        L.qconv_last_kernel.argtypes = []
+        L.qconv_last_kernel.restype = ctypes.c_char_p
         L.qconv_proj_default_tile.argtypes = [P(QConvDesc)]
         L.qconv_proj_tile_check.argtypes = [P(QConvDesc), _i32]
         L.qconv_prepared_proj_filter_bytes.argtypes = [P(QConvDesc), _i32, P(ctypes.c_size_t)]
@@ -280,6 +282,12 @@ def last_launch() -> dict:
     g, t, l = _i64(0), _i64(0), _i64(0)
     _check(lib().qconv_last_launch(ctypes.byref(g), ctypes.byref(t), ctypes.byref(l)), "qconv_last_launch")
     return {"grid": int(g.value), "threads": int(t.value), "lds_bytes": int(l.value)}
+
+
+def last_kernel() -> str:
+    """Name of the kernel this thread's most recent convolution launch ran: a
+    tile's, or ``direct_...`` (see qconv_last_kernel); "" before the first."""
+    return lib().qconv_last_kernel().decode()
 
 
 class ProbeGridMeetCall:

@@ -619,3 +619,12 @@ def test_validation_fuzz(q):
         L.qconv_default_tile(ctypes.byref(desc))
         L.qconv_proj_default_tile(ctypes.byref(desc))
     assert valid > 100 and running > 50
+
+
+def test_last_kernel_is_empty_before_a_launch(q):
+    import threading
+    names = []
+    t = threading.Thread(target=lambda: names.append(q.last_kernel()))
+    t.start()
+    t.join()
+    assert names == [""]

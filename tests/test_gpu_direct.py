@@ -133,6 +133,29 @@ def test_direct_layers(shape):
     assert direct or r * s > 31, "no tile took the direct kernels"
 
 
+def test_last_kernel_names_what_ran():
+    """A direct launch names a direct kernel, whichever tile's image it reads; a
+    schedule names its tile."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    dev = torch.device("cuda:0")
+    L = qi.Layer("names", 1, 14, 14, 128, 64, 3, 3, 1, 1)
+    d = L.desc()
+    x = torch.zeros(q.layout(d)["x_bytes"], dtype=torch.uint8, device=dev)
+    w = torch.zeros(q.layout(d)["w_bytes"], dtype=torch.uint8, device=dev)
+    for t in q.tiles():
+        if t["variant"] != 2 or q.tile_status(d, t["id"]) != 0:
+            continue
+        announce(f"last kernel, tile {t['name']}")
+        prep = q.prepare_filters(d, w, t["id"])
+        q.Conv2dCall(d, x, prep, schedule=dict(tile_id=t["id"]))()
+        assert q.last_kernel() == t["name"] and q.last_launch()["threads"] == t["threads"]
+        q.conv2d(d, x, prep, tile=t["id"], prepared=True)
+        assert q.last_kernel().startswith(f"direct_b4_k{t['frag_k']}_"), q.last_kernel()
+    torch.cuda.synchronize()
+
+
 def test_direct_projection():
     """The strided 3x3 and its projection in one direct launch, against the two
     layers run apart by the wide kernels (a forced launch knob keeps them there)."""
