@@ -286,6 +286,11 @@ int qconv2d(const qconv_desc *d, const void *x, const void *w, const qconv_epilo
  *   one they were prepared for (-1 resolves the same way for the same
  *   descriptor).  `splits` (1 = none) selects split-K, below; `workspace`
  *   may be NULL when splits == 1.  Results are identical to qconv2d.
+ *   Which kernel runs: with splits > 1 the tile's, split as asked.  Without a
+ *   split, and for wide tiles only, the library may run a direct kernel instead
+ *   (no input band in LDS; it reads the same prepared filters) where it estimates
+ *   that one to be faster; so do qconv2d_prepared_noalloc and qconv2d_proj.
+ *   qconv_last_kernel says which ran; qconv2d_scheduled always runs the tile's.
  */
 int qconv_prepared_filter_bytes(const qconv_desc *d, int32_t tile_id, size_t *bytes);
 int qconv_prepare_filters(const qconv_desc *d, const void *w_packed, int32_t tile_id, void *w_prepared,
@@ -457,7 +462,7 @@ int qconv_noalloc_limits(int64_t *scratch_bytes, int64_t *max_tiles);
  * qconv2d_scheduled -- qconv2d_prepared with every knob given; the prepared
  *   filters must be those of s->tile_id; `workspace` as for split-K above.
  *   qconv2d_prepared(..., tile_id, splits, ...) is the schedule
- *   {tile_id, splits, 0, 0, -1, 0}.
+ *   {tile_id, splits, 0, 0, -1, 0}, unless it takes a direct kernel.
  */
 typedef struct {
     int32_t tile_id;

@@ -1039,7 +1039,7 @@ bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_t
 // workspace in `workspace`.
 // wg_per_cu, band_buffers, xcd_order: the launch knobs of a qconv_schedule.
 // direct_ok: the layer may run on the direct kernels instead (no launch knob is
-// forced).
+// forced).  A caller's split-K is run as asked: it never becomes a direct launch.
 // x_nchw (then x is unused): int8 N x C x H x W activations, packed on the way
 // by the tile's fused instance, which also writes the packed copy to x_packed
 // when that is not null.
@@ -1240,7 +1240,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
             if (rc) return rc;
         }
     }
-    if (direct_ok && te.info.variant == QCONV_VARIANT_WIDE) {
+    if (direct_ok && splits == 1 && te.info.variant == QCONV_VARIANT_WIDE) {
         DirectArgs da;
         DirectLaunch dl;
         const DirectChoice dc = choose_direct(d, li, te.info, pl, wb, proj);

@@ -156,6 +156,44 @@ def test_last_kernel_names_what_ran():
     torch.cuda.synchronize()
 
 
+def _full_splits(q, d, tile):
+    """Split factors above one that leave no split empty."""
+    chunks = q.max_splits(d, tile)
+    return [s for s in range(2, chunks + 1) if -(-chunks // -(-chunks // s)) == s]
+
+
+def test_a_split_is_run_as_asked():
+    """`splits` > 1 launches tiles x splits workgroups of the wide tile, through
+    a workspace, the no-alloc scratch and with a projection, on layers that
+    run on direct kernels without a split."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    dev = torch.device("cuda:0")
+    L = qi.Layer("split", 1, 14, 14, 256, 64, 3, 3, 2, 1)
+    d = L.desc()
+    x = torch.zeros(q.layout(d)["x_bytes"], dtype=torch.uint8, device=dev)
+    w, w1 = (torch.zeros(q.layout(e)["w_bytes"], dtype=torch.uint8, device=dev) for e in (d, q.proj_desc(d)))
+    for t in q.tiles():
+        if t["variant"] != 2 or q.tile_status(d, t["id"]) != 0:
+            continue
+        tiles = -(-q.layout(d)["m"] // t["tile_p"]) * -(-L.k // t["tile_k"])
+        prep = q.prepare_filters(d, w, t["id"])
+        for splits in _full_splits(q, d, t["id"]):
+            want = dict(grid=tiles * splits, threads=t["threads"])
+            calls = {"workspace": q.Conv2dCall(d, x, prep, tile=t["id"], prepared=True, splits=splits),
+                     "no-alloc": lambda: q.conv2d(d, x, prep, tile=t["id"], prepared=True, splits=splits, noalloc=True)}
+            if q.proj_tile_status(d, t["id"]) == 0:
+                calls["projection"] = q.ProjConv2dCall(d, x, q.prepare_filters_proj(d, w, w1, t["id"]), tile=t["id"],
+                                                       splits=splits)
+            for name, call in calls.items():
+                announce(f"split {t['name']} {splits} {name}")
+                call()
+                launch = q.last_launch()
+                assert {f: launch[f] for f in want} == want, (t["name"], splits, name, launch)
+    torch.cuda.synchronize()
+
+
 def test_direct_projection():
     """The strided 3x3 and its projection in one direct launch, against the two
     layers run apart by the wide kernels (a forced launch knob keeps them there)."""
