@@ -367,6 +367,20 @@ int qconv2d_packing(const qconv_desc *d, const int8_t *x_nchw, void *x_packed, c
                     size_t w_prepared_bytes, const qconv_epilogue *epi, void *y, int32_t tile_id, void *stream);
 
 /*
+ * qconv2d_form -- a test and measurement aid: qconv2d_prepared without a split
+ * (y_proj not NULL: qconv2d_proj), with the kernel named instead of chosen.
+ *   form  -1: the tile's kernel; 0 .. qconv_form_count() - 1: that form of the
+ *         direct kernels (wave tile, depth, steps in flight, filters resident or
+ *         not), from the prepared filters of the wide tile `tile_id`
+ * QCONV_EINVAL for an unknown form, QCONV_EUNSUPPORTED where the form does not
+ * run the layer; other arguments, results and errors as qconv2d_prepared.
+ */
+int qconv_form_count(void);
+int qconv2d_form(const qconv_desc *d, const void *x, const void *w_prepared, size_t w_prepared_bytes,
+                 const qconv_epilogue *epi, void *y, const qconv_epilogue *epi_proj, void *y_proj, int32_t tile_id,
+                 int32_t form, void *stream);
+
+/*
  * Split-K over channel chunks (prepared filters, wide tiles).  The depth
  * C*R*S of the implicit GEMM (Sec. 2.1) is a sum over channel chunks of
  * `chunk_c` channels; with `splits` > 1 each output tile is computed by

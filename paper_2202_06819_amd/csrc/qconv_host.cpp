@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <initializer_list>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -898,22 +899,30 @@ double direct_estimate(const qconv_desc *d, int64_t m, const RouteSizes &z, cons
     return us;
 }
 
+// A layer of so many steps can run as `k`: some forms are compiled for one round
+// of their steps in flight, some for several only, and a projection's launch is
+// never resident.
+bool direct_fits(const qconv_desc *d, const DirectCandidate &k, int64_t steps, bool proj) {
+    const int lin = direct_lin(d) ? 1 : 0;
+    if (!lin && d->c % 64 != 0 && d->c > 64) return false;
+    if (k.lin != lin || (proj && k.c.resident) || k.c.wd > steps) return false;
+    if (k.two >= 0 && (k.two != 0) != direct_two_steps(d, k.c)) return false;
+    const int64_t wave_steps = (steps + k.c.wd - 1) / k.c.wd;
+    if (lin && wave_steps > k.c.la && (k.c.la < 4 || (k.c.la == 4 && k.c.np == 1))) return false;
+    return lin || k.c.la != 3 || wave_steps > 3;
+}
+
+int64_t direct_steps(const qconv_desc *d) { return (int64_t)d->r * d->s * ((d->c + 63) / 64); }
+
 DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_tile_info &t, const Plan &pl,
                            int64_t filter_bytes, bool proj) {
     const int lin = direct_lin(d) ? 1 : 0;
-    if (!lin && d->c % 64 != 0 && d->c > 64) return DirectChoice();
-    const RouteSizes z{li.x_bytes / 1e6, li.y_packed_bytes / 1e6, filter_bytes / 1e6, d->bits / 8.0,
-                       (int64_t)d->r * d->s * ((d->c + 63) / 64)};
+    const RouteSizes z{li.x_bytes / 1e6, li.y_packed_bytes / 1e6, filter_bytes / 1e6, d->bits / 8.0, direct_steps(d)};
     const DirectChoice none;
     const DirectCandidate *best = nullptr;
     double best_us = 1e30;
     for (const DirectCandidate &k : kDirectCandidates) {
-        if (k.lin != lin || (proj && k.c.resident) || k.c.wd > z.steps) continue;
-        if (k.two >= 0 && (k.two != 0) != direct_two_steps(d, k.c)) continue;
-        // some are compiled for one round of their steps in flight, some for several only
-        const int64_t wave_steps = (z.steps + k.c.wd - 1) / k.c.wd;
-        if (lin && wave_steps > k.c.la && (k.c.la < 4 || (k.c.la == 4 && k.c.np == 1))) continue;
-        if (!lin && k.c.la == 3 && wave_steps <= 3) continue;
+        if (!direct_fits(d, k, z.steps, proj)) continue;
         const double us = direct_estimate(d, li.m, z, k);
         if (us < best_us) {
             best_us = us;
@@ -975,7 +984,7 @@ bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_t
     if (li.x_bytes + 2 * back + ((int64_t)d->r * d->w + d->s + 2) * xpix >= (1ll << 31)) return false;
     const bool lin = direct_lin(d);
     if (!lin && d->c % 64 != 0 && d->c > 64) return false;
-    const int64_t steps = taps * ((d->c + 63) / 64), wave_steps = (steps + c.wd - 1) / c.wd;
+    const int64_t steps = direct_steps(d), wave_steps = (steps + c.wd - 1) / c.wd;
     // (two steps a load wherever the channels are whole pairs of steps)
     const bool two = direct_two_steps(d, c);
     out.inst = direct_instance(d->bits, t.frag_k, c.np, c.fp, ext, c.la, wave_steps > c.la, lin, c.resident, two);
@@ -1038,17 +1047,19 @@ bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_t
 // splits > 1 (prepared filters only): split-K over channel chunks with its
 // workspace in `workspace`.
 // wg_per_cu, band_buffers, xcd_order: the launch knobs of a qconv_schedule.
-// direct_ok: the layer may run on the direct kernels instead (no launch knob is
-// forced).  A caller's split-K is run as asked: it never becomes a direct launch.
+// form: kFormTile runs the tile's kernel; kFormAuto lets an unsplit layer run on a
+// direct kernel instead (no launch knob is forced, and a caller's split-K never
+// becomes a direct launch); from 0 on, that one of the direct candidates.
 // x_nchw (then x is unused): int8 N x C x H x W activations, packed on the way
 // by the tile's fused instance, which also writes the packed copy to x_packed
 // when that is not null.
+constexpr int32_t kFormTile = -1, kFormAuto = -2;
 int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, size_t w_bytes_given,
              const qconv_epilogue *epi, void *y, void *workspace, size_t workspace_bytes, int32_t tile_id,
              int32_t splits, void *stream, int32_t wg_per_cu = 0, int32_t band_buffers = 0,
              int32_t xcd_order = -1, int32_t ablation = 0, const int8_t *x_nchw = nullptr,
              void *x_packed = nullptr, bool noalloc = false, const qconv_epilogue *epi_proj = nullptr,
-             void *y_proj = nullptr, bool direct_ok = false) {
+             void *y_proj = nullptr, int32_t form = kFormTile) {
     qconv_layout_info li;
     qconv_desc kd;
     int rc = kernel_desc(d, &kd, &li);
@@ -1215,7 +1226,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
                                        (hipStream_t)stream);
             if (e != hipSuccess) return fail(QCONV_EHIP, "pack launch: %s", hipGetErrorString(e));
             return run_conv(d, x_packed, w, prepared, w_bytes_given, epi, y, nullptr, 0, tile_id, 1, stream, wg_per_cu,
-                            band_buffers, xcd_order, ablation, nullptr, nullptr, false, nullptr, nullptr, true);
+                            band_buffers, xcd_order, ablation, nullptr, nullptr, false, nullptr, nullptr, kFormAuto);
         }
         launch = te.fused.launch;
         kernel = te.fused.kernel;
@@ -1240,10 +1251,12 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
             if (rc) return rc;
         }
     }
-    if (direct_ok && splits == 1 && te.info.variant == QCONV_VARIANT_WIDE) {
+    if (form != kFormTile && splits == 1 && te.info.variant == QCONV_VARIANT_WIDE) {
         DirectArgs da;
         DirectLaunch dl;
-        const DirectChoice dc = choose_direct(d, li, te.info, pl, wb, proj);
+        const bool fits = form < 0 || direct_fits(d, kDirectCandidates[form], direct_steps(d), proj);
+        const DirectChoice dc = form < 0 ? choose_direct(d, li, te.info, pl, wb, proj)
+                                         : fits ? kDirectCandidates[form].c : DirectChoice();
         if (plan_direct(d, li, te.info, pl, ext, wb, x, w, proj, dc, da, dl)) {
             da.mode = requant ? QCONV_OUT_REQUANT : QCONV_OUT_RAW_I32;
             da.res = requant ? static_cast<const uint8_t *>(epi->residual) : nullptr;
@@ -1271,6 +1284,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
             return QCONV_OK;
         }
     }
+    if (form >= 0) return fail(QCONV_EUNSUPPORTED, "direct form %d does not run this layer from tile %s", form, te.info.name);
     ConvArgs a;
     fill_args(a, d, li, te, pl);
     a.xptr = static_cast<const uint8_t *>(x);
@@ -1466,14 +1480,25 @@ int qconv2d_prepared(const qconv_desc *d, const void *x, const void *w_prepared,
                      size_t workspace_bytes, void *stream) {
     g_err[0] = 0;
     return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, workspace, workspace_bytes, tile_id, splits,
-                    stream, 0, 0, -1, 0, nullptr, nullptr, false, nullptr, nullptr, true);
+                    stream, 0, 0, -1, 0, nullptr, nullptr, false, nullptr, nullptr, kFormAuto);
 }
 
 int qconv2d_prepared_noalloc(const qconv_desc *d, const void *x, const void *w_prepared, size_t w_prepared_bytes,
                              const qconv_epilogue *epi, void *y, int32_t tile_id, int32_t splits, void *stream) {
     g_err[0] = 0;
     return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, nullptr, 0, tile_id, splits, stream, 0, 0, -1, 0,
-                    nullptr, nullptr, true, nullptr, nullptr, true);
+                    nullptr, nullptr, true, nullptr, nullptr, kFormAuto);
+}
+
+int qconv_form_count(void) { return (int)std::size(kDirectCandidates); }
+
+int qconv2d_form(const qconv_desc *d, const void *x, const void *w_prepared, size_t w_prepared_bytes,
+                 const qconv_epilogue *epi, void *y, const qconv_epilogue *epi_proj, void *y_proj, int32_t tile_id,
+                 int32_t form, void *stream) {
+    g_err[0] = 0;
+    if (form < kFormTile || form >= qconv_form_count()) return fail(QCONV_EINVAL, "unknown form %d", form);
+    return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, nullptr, 0, tile_id, 1, stream, 0, 0, -1, 0,
+                    nullptr, nullptr, false, epi_proj, y_proj, form);
 }
 
 // The tile a layer with a fused projection runs (tile_id, or the built-in
@@ -1581,7 +1606,7 @@ int qconv2d_proj(const qconv_desc *d, const void *x, const void *w_prepared, siz
     g_err[0] = 0;
     if (!y_proj) return fail(QCONV_EINVAL, "y_proj must be non-NULL");
     return run_conv(d, x, w_prepared, true, w_prepared_bytes, epi, y, workspace, workspace_bytes, tile_id, splits,
-                    stream, 0, 0, -1, 0, nullptr, nullptr, false, epi_proj, y_proj, true);
+                    stream, 0, 0, -1, 0, nullptr, nullptr, false, epi_proj, y_proj, kFormAuto);
 }
 
 int qconv_noalloc_limits(int64_t *scratch_bytes, int64_t *max_tiles) {

@@ -135,6 +135,9 @@ def lib() -> ctypes.CDLL:
         L.qconv_proj_workspace_bytes.argtypes = [P(QConvDesc), _i32, _i32, P(ctypes.c_size_t)]
         L.qconv2d_proj.argtypes = [P(QConvDesc), _vp, _vp, ctypes.c_size_t, P(QConvEpilogue), _vp,
                                    P(QConvEpilogue), _vp, _i32, _i32, _vp, ctypes.c_size_t, _vp]
+        L.qconv_form_count.argtypes = []
+        L.qconv2d_form.argtypes = [P(QConvDesc), _vp, _vp, ctypes.c_size_t, P(QConvEpilogue), _vp, P(QConvEpilogue),
+                                   _vp, _i32, _i32, _vp]
         for f in ("qconv_layout", "qconv_pack", "qconv2d", "qconv_tile_count", "qconv_tile_get", "qconv_tile_check",
                   "qconv_default_tile", "qconv_selftest", "qconv_prepared_filter_bytes", "qconv_prepare_filters",
                   "qconv2d_prepared", "qconv_workspace_bytes", "qconv_max_splits", "qconv_probe_mfma_i8", "qconv_schedule_check", "qconv2d_scheduled", "qconv_unroll", "qconv_pack_interleaved",
@@ -142,7 +145,7 @@ def lib() -> ctypes.CDLL:
                   "qconv_probe_grid_meet", "qconv_probe_mfma_i8_shape",
                   "qconv_last_launch", "qconv_proj_default_tile", "qconv_proj_tile_check",
                   "qconv_prepared_proj_filter_bytes", "qconv_prepare_filters_proj", "qconv_proj_workspace_bytes",
-                  "qconv2d_proj"):
+                  "qconv2d_proj", "qconv_form_count", "qconv2d_form"):
             getattr(L, f).restype = ctypes.c_int
         _lib = L
         return L
@@ -282,6 +285,11 @@ def last_launch() -> dict:
     g, t, l = _i64(0), _i64(0), _i64(0)
     _check(lib().qconv_last_launch(ctypes.byref(g), ctypes.byref(t), ctypes.byref(l)), "qconv_last_launch")
     return {"grid": int(g.value), "threads": int(t.value), "lds_bytes": int(l.value)}
+
+
+def form_count() -> int:
+    """Forms of the direct kernels that ``form=`` can name (see qconv2d_form)."""
+    return int(lib().qconv_form_count())
 
 
 def last_kernel() -> str:
@@ -521,6 +529,12 @@ class PackCall:
         return self.out
 
 
+def _check_form(form, splits, schedule=None) -> None:
+    """A named kernel (qconv2d_form) takes no split and no schedule."""
+    if form is not None and (int(splits) != 1 or schedule is not None):
+        raise QConvError(EINVAL, "form runs without a split and without a schedule")
+
+
 class Conv2dCall:
     """A qconv2d call with its arguments marshalled once; ``()`` enqueues it.
 
@@ -532,13 +546,15 @@ class Conv2dCall:
                  out: torch.Tensor | None = None, tile: int = -1, stream=None, prepared: bool = False,
                  splits: int = 1, workspace: torch.Tensor | None = None, schedule: dict | None = None,
                  bias: torch.Tensor | None = None, residual: torch.Tensor | None = None,
-                 residual_signed: bool = False):
+                 residual_signed: bool = False, form: int | None = None):
         """With `schedule` (a dict of qconv_schedule knobs; `w` prepared for its
-        tile) the call goes through qconv2d_scheduled."""
+        tile) the call goes through qconv2d_scheduled, with `form` (prepared
+        filters, no split) through qconv2d_form."""
         if schedule is not None:
             prepared = True
             tile = int(schedule.get("tile_id", tile))
             splits = int(schedule.get("splits", 1))
+        _check_form(form, splits, schedule)
         self.desc = make_desc(d)
         info = layout(d)
         bits = self.desc.bits
@@ -575,6 +591,11 @@ class Conv2dCall:
                               w.numel() * w.element_size(), ctypes.byref(self.epi), _dev_ptr(out, "y", y_bytes),
                               ctypes.byref(self.schedule), ws_ptr, ws_bytes, _vp(_stream(stream)))
                 self._fn = lib().qconv2d_scheduled
+            elif form is not None:
+                self._args = (ctypes.byref(self.desc), _dev_ptr(x, "x", info["x_bytes"]), _dev_ptr(w, "w", wb),
+                              w.numel() * w.element_size(), ctypes.byref(self.epi), _dev_ptr(out, "y", y_bytes),
+                              None, None, self.tile, int(form), _vp(_stream(stream)))
+                self._fn = lib().qconv2d_form
             else:
                 self._args = (ctypes.byref(self.desc), _dev_ptr(x, "x", info["x_bytes"]), _dev_ptr(w, "w", wb),
                               w.numel() * w.element_size(), ctypes.byref(self.epi), _dev_ptr(out, "y", y_bytes),
@@ -653,14 +674,16 @@ class ProjConv2dCall:
     each output's own multipliers, shift, ReLU, clamp and optional bias
     (``proj`` holds the projection's: dict(mult=, shift=, relu=, clamp=, bias=)).
     `splits` > 1 is split-K, with a zero-filled `workspace` of
-    :func:`proj_workspace_bytes` (made here when not given).
+    :func:`proj_workspace_bytes` (made here when not given).  `form` (no split)
+    names the kernel (qconv2d_form).
     """
 
     def __init__(self, d: dict, x: torch.Tensor, w_prepared: torch.Tensor, *, tile: int = -1, requant: bool = False,
                  mult: torch.Tensor | None = None, shift: int = 20, relu: bool = True, clamp: tuple = (0, 15),
                  bias: torch.Tensor | None = None, proj: dict | None = None, out: torch.Tensor | None = None,
                  out_proj: torch.Tensor | None = None, splits: int = 1, workspace: torch.Tensor | None = None,
-                 stream=None):
+                 stream=None, form: int | None = None):
+        _check_form(form, splits)
         self.desc = make_desc(d)
         info = layout(d)
         bits = self.desc.bits
@@ -697,6 +720,9 @@ class ProjConv2dCall:
                       _dev_ptr(out_proj, "y_proj", y_bytes), self.tile, self.splits, ws_ptr, ws_bytes,
                       _vp(_stream(stream)))
         self._fn = lib().qconv2d_proj
+        if form is not None:   # (tile, form and stream after the pointers: no split)
+            self._args = (*self._args[:9], int(form), self._args[-1])
+            self._fn = lib().qconv2d_form
 
     def __call__(self):
         _check(self._fn(*self._args), "qconv2d_proj")

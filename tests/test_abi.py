@@ -628,3 +628,21 @@ def test_last_kernel_is_empty_before_a_launch(q):
     t.start()
     t.join()
     assert names == [""]
+
+
+def test_forms_are_checked_before_anything_runs(q):
+    """Unknown forms, forms on staged tiles and forms beside a split are refused on the host."""
+    d = D(n=1, h=14, w=14, c=64, k=64)
+    L = q.lib()
+    n = q.form_count()
+    assert n >= 2
+    wide = next(t["id"] for t in q.tiles() if t["variant"] == 2 and q.tile_status(d, t["id"]) == 0)
+    staged = next(t["id"] for t in q.tiles() if t["variant"] == 0 and q.tile_status(d, t["id"]) == 0)
+    args = (ctypes.byref(q.make_desc(d)), 1 << 20, 1 << 30, 1 << 28, None, 1 << 34, None, None)
+    for form in (-3, -2, n, 1 << 20):
+        assert L.qconv2d_form(*args, wide, form, None) == q.EINVAL
+    assert L.qconv2d_form(*args, staged, 0, None) == q.EUNSUPPORTED
+    with pytest.raises(q.QConvError):
+        q.Conv2dCall(d, None, None, tile=wide, prepared=True, splits=2, form=0)
+    with pytest.raises(q.QConvError):
+        q.ProjConv2dCall(d, None, None, tile=wide, splits=2, form=-1)

@@ -1,7 +1,9 @@
-"""Prepared layers that run on the direct kernels: small layers at the edges of
-their tiles (pixel fragments, channel pairs and chunks, padding wider than the
-filter, the end of the tensor) and every form of their epilogue, from the
-filter image of every wide tile, against the oracle's sums."""
+"""Prepared layers that the library moves to the direct kernels by itself: small
+layers at the edges of their tiles (pixel fragments, channel pairs and chunks,
+padding wider than the filter, the end of the tensor) and every form of their
+epilogue, from the filter image of every wide tile, against the oracle's sums.
+Layers this small take the depth form with one round of steps in flight;
+test_gpu_direct_forms.py names every form in turn."""
 import numpy as np
 import pytest
 
@@ -18,7 +20,7 @@ SHAPES = [
     (1, 4, 4, 96, 40, 1, 1, 1, 0, 4),       # 16 pixels, a chunk and a half: the last load ends at the tensor's end
     (1, 1, 17, 160, 72, 1, 1, 1, 0, 4),     # 17 pixels
     (3, 9, 7, 256, 64, 1, 1, 1, 0, 4),
-    (2, 11, 5, 512, 136, 1, 1, 1, 0, 4),    # several rounds of steps
+    (2, 11, 5, 512, 136, 1, 1, 1, 0, 4),    # eight steps, all in flight
     (2, 9, 9, 128, 32, 1, 1, 2, 0, 4),      # strided 1x1
     (1, 7, 7, 32, 64, 3, 3, 1, 1, 4),       # half a chunk under a 3x3
     (2, 7, 18, 64, 72, 3, 3, 1, 1, 4),      # rows of more than one fragment
@@ -110,8 +112,7 @@ def test_direct_layers(shape):
         announce(f"direct {shape} {t['name']} raw")
         y = q.conv2d(d, xp, prep, tile=t["id"], prepared=True)
         torch.cuda.synchronize()
-        launch = q.last_launch()
-        direct += launch["lds_bytes"] == 0 or launch["threads"] != t["threads"]
+        direct += q.last_kernel().startswith("direct_")
         assert_same(y.cpu().numpy(), acc.astype(np.int32), f"{shape} {t['name']} raw")
         for name, f in forms:
             if t["frag_p"] != 2 and "residual" not in name and name != "full range":
@@ -211,6 +212,7 @@ def test_direct_projection():
         w1 = q.pack(torch.from_numpy(g.integers(-8, 8, size=(k, c, 1, 1)).astype(np.int8)).to(dev), bits, True)
         m3, m1 = (torch.from_numpy(g.integers(1 << 14, 1 << 15, size=k).astype(np.int32)).to(dev) for _ in range(2))
         b1 = torch.from_numpy(g.integers(-200, 200, size=k).astype(np.int32)).to(dev)
+        direct = 0
         for t in q.tiles():
             if q.proj_tile_status(d, t["id"]) != 0 or q.tile_status(dp, t["id"]) != 0:
                 continue
@@ -218,6 +220,7 @@ def test_direct_projection():
             y, yp = q.ProjConv2dCall(d, x, q.prepare_filters_proj(d, w3, w1, t["id"]), tile=t["id"], requant=True,
                                      mult=m3, shift=22, relu=False, clamp=(lo, hi),
                                      proj=dict(mult=m1, shift=20, relu=False, clamp=(lo, hi), bias=b1))()
+            direct += q.last_kernel().startswith("direct_")
             sch = dict(tile_id=t["id"], wg_per_cu=1)
             w = [q.Conv2dCall(d, x, q.prepare_filters(d, w3, t["id"]), requant=True, mult=m3, shift=22, relu=False,
                               clamp=(lo, hi), schedule=sch)(),
@@ -226,3 +229,4 @@ def test_direct_projection():
             torch.cuda.synchronize()
             assert_same(y.cpu().numpy(), w[0].cpu().numpy(), f"projection {t['name']} layer")
             assert_same(yp.cpu().numpy(), w[1].cpu().numpy(), f"projection {t['name']} projection")
+        assert direct, f"no tile took the direct kernels for {n}x{h}x{h} {c}->{k}"
