@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import qconv_inputs as qi
-from _util import announce, assert_same, oracle_threads
+from _util import announce, assert_same, epilogue_forms, oracle_threads, packed_values, requantised
 
 pytestmark = pytest.mark.gpu
 
@@ -38,53 +38,6 @@ SHAPES = [
 ]
 
 
-def _requant(acc, mult, shift, lo, hi, bias=None, res=None):
-    a = acc.astype(object) if shift > 40 else acc.astype(np.int64)
-    if bias is not None:
-        a = a + bias
-    t = (a * mult + (1 << (shift - 1))) >> shift
-    if res is not None:
-        t = t + res
-    return np.clip(t.astype(np.int64) if shift <= 40 else np.array(t, dtype=np.int64), lo, hi)
-
-
-def _pack(y, bits):
-    if bits == 8:
-        return y.astype(np.int8)
-    y = (y & 15).astype(np.uint32).reshape(*y.shape[:-1], -1, 8)
-    return np.bitwise_or.reduce(y << (4 * np.arange(8, dtype=np.uint32)), axis=-1).astype(np.uint32)
-
-
-def _forms(g, k, bits, spread, y_shape):
-    """(name, arguments) of the epilogues: both output ranges, a clamp inside
-    one, multipliers past 24 bits, extreme shifts, and biases and residuals of
-    either signedness."""
-    mult = g.integers(1 << 14, 1 << 15, size=k).astype(np.int32)
-    span = 8 if bits == 4 else 64
-    sh = int(max(1, min(40, round(np.log2(max(spread, 1) * 2 ** 14.5 / span)))))
-    full = (0, 15) if bits == 4 else (-128, 127)
-    other = (-8, 7) if bits == 4 else (0, 127)
-    signed = mult * g.choice([-1, 1], size=k).astype(np.int32)
-    res_u = g.integers(0, 16 if bits == 4 else 256, size=y_shape)
-    res_s = g.integers(-8 if bits == 4 else -128, 8 if bits == 4 else 128, size=y_shape)
-    return [
-        ("full range", dict(mult=mult, shift=sh, clamp=full)),
-        ("other range", dict(mult=signed, shift=sh, clamp=other)),
-        ("inside a range", dict(mult=mult, shift=sh, clamp=(1, 6))),
-        ("wide multipliers", dict(mult=(mult.astype(np.int64) * 40000).clip(max=2 ** 31 - 1).astype(np.int32),
-                                  shift=min(sh + 15, 62), clamp=full)),
-        ("shift 1", dict(mult=np.ones(k, np.int32), shift=1, clamp=other)),
-        ("shift 62", dict(mult=mult, shift=62, clamp=full)),
-        ("bias", dict(mult=mult, shift=sh, clamp=full, bias=g.integers(-300, 300, size=k).astype(np.int32))),
-        ("bias past the f32 form", dict(mult=mult, shift=sh, clamp=full,
-                                        bias=g.integers(-(1 << 22), 1 << 22, size=k).astype(np.int32))),
-        ("unsigned residual", dict(mult=mult, shift=sh, clamp=full, res=res_u, res_signed=False)),
-        ("signed residual and bias", dict(mult=signed, shift=sh, clamp=other, res=res_s, res_signed=True,
-                                          bias=g.integers(-300, 300, size=k).astype(np.int32))),
-        ("residual of the other signedness", dict(mult=mult, shift=sh, clamp=full, res=res_s, res_signed=True)),
-    ]
-
-
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_direct_layers(shape):
     import torch
@@ -103,7 +56,7 @@ def test_direct_layers(shape):
                              threads=oracle_threads())["acc"].reshape(n, L.p, L.q, k)
     xp = q.pack(torch.from_numpy(x).to(dev), bits, signed)
     wp = q.pack(torch.from_numpy(wt).to(dev), bits, True)
-    forms = _forms(g, k, bits, float(np.abs(acc).mean()), acc.shape)
+    forms = epilogue_forms(g, k, bits, float(np.abs(acc).mean()), acc.shape)
     direct = 0
     for t in q.tiles():
         if t["variant"] != 2 or q.tile_status(d, t["id"]) != 0:
@@ -123,12 +76,12 @@ def test_direct_layers(shape):
             if "bias" in f:
                 kw["bias"] = torch.from_numpy(f["bias"]).to(dev)
             if "res" in f:
-                packed = _pack(f["res"], bits)
+                packed = packed_values(f["res"], bits)
                 kw.update(residual=torch.from_numpy(packed.view(np.int32) if bits == 4 else packed).to(dev),
                           residual_signed=f["res_signed"])
             y = q.conv2d(d, xp, prep, tile=t["id"], prepared=True, **kw)
             torch.cuda.synchronize()
-            want = _pack(_requant(acc, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f.get("bias"),
+            want = packed_values(requantised(acc, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f.get("bias"),
                                   f.get("res")), bits)
             assert_same(y.cpu().numpy(), want, f"{shape} {t['name']} {name}")
     assert direct or r * s > 31, "no tile took the direct kernels"

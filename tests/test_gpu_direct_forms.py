@@ -9,8 +9,7 @@ import pytest
 
 import oracle
 import qconv_inputs as qi
-from _util import announce, assert_same, oracle_threads
-from test_gpu_direct import _forms, _pack, _requant
+from _util import announce, assert_same, epilogue_forms, oracle_threads, packed_values, requantised
 
 pytestmark = pytest.mark.gpu
 
@@ -93,7 +92,7 @@ def _args(f, bits, dev):
     if "bias" in f:
         kw["bias"] = torch.from_numpy(f["bias"]).to(dev)
     if "res" in f:
-        packed = _pack(f["res"], bits)
+        packed = packed_values(f["res"], bits)
         kw.update(residual=torch.from_numpy(packed.view(np.int32) if bits == 4 else packed).to(dev),
                   residual_signed=f["res_signed"])
     return kw
@@ -112,8 +111,8 @@ def test_every_form_and_epilogue(bits):
         xp = q.pack(torch.from_numpy(x).to(dev), bits, bits == 8)
         wp = q.pack(torch.from_numpy(wt).to(dev), bits, True)
         wants, kws = {"raw": acc.astype(np.int32)}, {"raw": {}}
-        for name, f in _forms(g, d["k"], bits, float(np.abs(acc).mean()), acc.shape):
-            wants[name] = _pack(_requant(acc, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f.get("bias"),
+        for name, f in epilogue_forms(g, d["k"], bits, float(np.abs(acc).mean()), acc.shape):
+            wants[name] = packed_values(requantised(acc, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f.get("bias"),
                                          f.get("res")), bits)
             kws[name] = _args(f, bits, dev)
         want = {name: torch.from_numpy(np.ascontiguousarray(v).view(np.int32 if v.dtype != np.int8 else np.int8)).to(dev)
@@ -160,11 +159,11 @@ def test_every_form_of_a_projection(bits):
                                   pad=(0, 0), threads=oracle_threads())["acc"]
         xp = q.pack(torch.from_numpy(x).to(dev), bits, bits == 8)
         p3, p1 = (q.pack(torch.from_numpy(f).to(dev), bits, True) for f in (w3, w1))
-        f3, f1 = (dict(_forms(g, k, bits, float(np.abs(a).mean()), a.shape))["bias"] for a in (acc, acc1))
+        f3, f1 = (dict(epilogue_forms(g, k, bits, float(np.abs(a).mean()), a.shape))["bias"] for a in (acc, acc1))
         k3, k1 = _args(f3, bits, dev), _args(f1, bits, dev)
         k1.pop("requant")
         wants = [(acc.astype(np.int32), acc1.astype(np.int32))]
-        wants.append(tuple(_pack(_requant(a, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f["bias"]), bits)
+        wants.append(tuple(packed_values(requantised(a, f["mult"].astype(np.int64), f["shift"], *f["clamp"], f["bias"]), bits)
                            for a, f in ((acc, f3), (acc1, f1))))
         for t in q.tiles():
             if q.proj_tile_status(d, t["id"]) != 0:

@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import qconv_inputs as qi
-from _util import announce, assert_same, gpu_layer, oracle_threads, ref_layer, stress_shift, unroll_def
+from _util import announce, assert_same, conv2d_prepared, gpu_layer, oracle_threads, ref_layer, stress_shift, unroll_def
 
 pytestmark = pytest.mark.gpu
 
@@ -550,14 +550,12 @@ def test_bias_and_residual_every_tile(shape):
             assert_same(y.cpu().numpy(), want, f"{name} tile {tid} case {ci}")
             if wide:
                 announce(f"{name} tile {tid} case {ci} prepared")
-                y = q.conv2d(L.desc(), xp, wprep, tile=tid, prepared=True, **kw)
+                y = conv2d_prepared(L.desc(), xp, wprep, tid, **kw)
                 torch.cuda.synchronize()
                 assert_same(y.cpu().numpy(), want, f"{name} tile {tid} case {ci} prepared")
                 if res is not None:
                     announce(f"{name} tile {tid} case {ci} in place")
-                    yy = res.clone()
-                    kw_in = dict(kw, residual=yy)
-                    q.conv2d(L.desc(), xp, wprep, tile=tid, prepared=True, out=yy, **kw_in)
+                    yy = conv2d_prepared(L.desc(), xp, wprep, tid, in_place=res, **kw)
                     torch.cuda.synchronize()
                     assert_same(yy.cpu().numpy(), want, f"{name} tile {tid} case {ci} in place")
                 chunks = q.max_splits(L.desc(), tid)
@@ -704,8 +702,7 @@ def test_stem_7x7_by_patch_unrolling(fold):
         assert_same(y.cpu().numpy(), ref["y_packed"], f"stem {fold} {tt['name']}")
         if tt["variant"] == 2:
             wprep = q.prepare_filters(d, wu, tt["id"])
-            y = q.conv2d(d, xu, wprep, tile=tt["id"], prepared=True)
-            torch.cuda.synchronize()
+            y = conv2d_prepared(d, xu, wprep, tt["id"])
             assert_same(y.cpu().numpy(), ref["acc"], f"stem {fold} {tt['name']} prepared raw")
     assert ran >= 2
 

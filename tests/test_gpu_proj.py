@@ -2,7 +2,8 @@
 element by element: both outputs -- the 3x3 layer's and the projection's --
 as raw int32 accumulators and requantised (each with its own multipliers,
 shift, clamp and optional bias), on every tile that has a projection
-instance, without and with split-K (each split call made twice on one
+instance, without a split (on the tile's own kernel and on the one the
+library takes) and with split-K (each split call made twice on one
 workspace), on small ragged shapes (odd sizes, several channel chunks, 4-bit
 and 8-bit, stride 2 and 1) and on the three stage entries of the ResNet-18
 stacks at full size in the configuration the chain runs."""
@@ -73,16 +74,18 @@ def _check_layer(L, t, tile, shifts, label, splits=(1,)):
             refs[(shift, shift2, bias)] = _refs(L, t, shift, shift2, bias)
         return refs[(shift, shift2, bias)]
 
-    for sp in splits:
+    # without a split on the tile's own kernel and on the one the library takes
+    for sp, form in [(sp, form) for sp in splits for form in ((-1, None) if sp == 1 else (None,))]:
         nws = qconv.proj_workspace_bytes(d, tile, sp)
         ws = torch.zeros(nws, dtype=torch.uint8, device=dev) if nws else None
         rounds = 2 if sp > 1 else 1   # a split call leaves its workspace ready for the next
-        announce(f"proj {label} {L.name} tile {tile} splits {sp} raw")
-        call = qconv.ProjConv2dCall(d, xp, wprep, tile=tile, splits=sp, workspace=ws)
+        announce(f"proj {label} {L.name} tile {tile} splits {sp} form {form} raw")
+        call = qconv.ProjConv2dCall(d, xp, wprep, tile=tile, splits=sp, workspace=ws, form=form)
         r3, r1 = ref(shifts[0][0], shifts[0][1], False)
         for rnd in range(rounds):
             y, yp = call()
             torch.cuda.synchronize()
+            assert form is None or qconv.last_kernel() == qconv.tiles()[tile]["name"]
             assert_same(y.cpu().numpy(), r3["acc"], f"{L.name} tile {tile} splits {sp} ({rnd}): 3x3 accumulators")
             assert_same(yp.cpu().numpy(), r1["acc"], f"{L.name} tile {tile} splits {sp} ({rnd}): projection "
                                                      f"accumulators")
@@ -92,7 +95,8 @@ def _check_layer(L, t, tile, shifts, label, splits=(1,)):
                 call = qconv.ProjConv2dCall(d, xp, wprep, tile=tile, requant=True, mult=dv["mult"], shift=shift,
                                             relu=e.relu, clamp=(e.lo, e.hi), bias=dv["bias"] if bias else None,
                                             proj=dict(mult=dv["mult2"], shift=shift2, relu=False, clamp=(e.lo, e.hi),
-                                                      bias=dv["bias2"] if bias else None), splits=sp, workspace=ws)
+                                                      bias=dv["bias2"] if bias else None), splits=sp, workspace=ws,
+                                            form=form)
                 r3, r1 = ref(shift, shift2, bias)
                 for rnd in range(rounds):
                     y, yp = call()

@@ -1,5 +1,6 @@
 """GPU parity over many random shapes: every tile that runs a shape, from packed
-and from prepared filters, with a random split-K factor on the wide tiles and,
+and from prepared filters (both on the tile's own kernel and on the one the
+library takes), with a random split-K factor on the wide tiles and,
 for 3x3 shapes, the pack fused into the convolution.  Shapes mix ragged pixel
 counts and channel counts, strides 1-3, paddings beyond the filter's half
 width, filters from 1x1 to 7x7 (non-square ones too), signed and unsigned
@@ -15,7 +16,7 @@ import pytest
 
 import oracle
 import qconv_inputs as qi
-from _util import announce, assert_same, gpu_layer, oracle_threads, random_layer, ref_layer, stress_shift
+from _util import announce, assert_same, conv2d_prepared, gpu_layer, oracle_threads, random_layer, ref_layer, stress_shift
 
 pytestmark = pytest.mark.gpu
 
@@ -152,11 +153,10 @@ def test_random_shapes_bias_residual(block):
             if tiles_all[tid]["variant"] != 2:
                 continue
             wprep = q.prepare_filters(d, wp, tid)
-            y = q.conv2d(d, xp, wprep, tile=tid, prepared=True, **kw)
+            y = conv2d_prepared(d, xp, wprep, tid, **kw)
             torch.cuda.synchronize()
             assert_same(y.cpu().numpy(), want, f"{L.name} tile {tid} prepared")
-            yy = res.clone()
-            q.conv2d(d, xp, wprep, tile=tid, prepared=True, out=yy, **dict(kw, residual=yy))
+            yy = conv2d_prepared(d, xp, wprep, tid, in_place=res, **kw)
             torch.cuda.synchronize()
             assert_same(yy.cpu().numpy(), want, f"{L.name} tile {tid} in place")
             most = q.max_splits(d, tid)
@@ -353,7 +353,7 @@ def test_random_shapes_per_axis_strides_and_paddings():
             if tiles_all[tid]["variant"] != 2:
                 continue
             wprep = q.prepare_filters(d, wp, tid)
-            y = q.conv2d(d, xp, wprep, tile=tid, prepared=True)
+            y = conv2d_prepared(d, xp, wprep, tid)
             torch.cuda.synchronize()
             assert_same(y.cpu().numpy(), ref["acc"], f"{d} tile {tid} prepared")
             most = q.max_splits(d, tid)

@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import qconv_inputs as qi
-from _util import announce, assert_same, oracle_threads, stress_shift
+from _util import announce, assert_same, conv2d_prepared, oracle_threads, stress_shift
 
 pytestmark = pytest.mark.gpu
 
@@ -37,13 +37,19 @@ def test_workload_layers_full_size(cfg):
         tile, splits = sweep.tuned_config(d, e is not None)
         wprep = qconv.prepare_filters(d, wp, tile)
         ws = qconv.make_workspace(d, tile, splits, dev)
+
+        def conv(**kw):   # the launch that is timed; without a split also the tile's own kernel
+            if splits == 1:
+                return conv2d_prepared(d, xp, wprep, tile, **kw)
+            return qconv.Conv2dCall(d, xp, wprep, tile=tile, prepared=True, splits=splits, workspace=ws, **kw)()
+
         stride, pad = (L.stride, L.stride), (L.pad, L.pad)
         kw = dict(bits=L.bits, x_signed=L.x_signed, w_signed=L.w_signed, stride=stride, pad=pad,
                   threads=oracle_threads())
         if e is None:
             ref = oracle.qconv_layer(t["x"], t["w"], **kw)
             announce(f"workload {cfg} {L.name} raw, tile {tile} splits {splits}")
-            y = qconv.Conv2dCall(d, xp, wprep, tile=tile, prepared=True, splits=splits, workspace=ws)()
+            y = conv()
             torch.cuda.synchronize()
             assert_same(y.cpu().numpy(), ref["acc"], f"workload {cfg} {L.name} raw")
             continue
@@ -54,13 +60,12 @@ def test_workload_layers_full_size(cfg):
             ref = oracle.qconv_layer(t["x"], t["w"], mult=t["mult"], shift=shift, relu=e.relu, lo=e.lo, hi=e.hi,
                                      **kw)
             announce(f"workload {cfg} {L.name} shift {shift}, tile {tile} splits {splits}")
-            y = qconv.Conv2dCall(d, xp, wprep, requant=True, mult=mult, shift=shift, relu=e.relu,
-                                 clamp=(e.lo, e.hi), tile=tile, prepared=True, splits=splits, workspace=ws)()
+            y = conv(requant=True, mult=mult, shift=shift, relu=e.relu, clamp=(e.lo, e.hi))
             torch.cuda.synchronize()
             assert_same(y.cpu().numpy(), ref["y_packed"], f"workload {cfg} {L.name} shift {shift}")
             if cfg in (2, 3) and shift == e.shift:
                 announce(f"workload {cfg} {L.name} raw")
-                y = qconv.Conv2dCall(d, xp, wprep, tile=tile, prepared=True, splits=splits, workspace=ws)()
+                y = conv()
                 torch.cuda.synchronize()
                 assert_same(y.cpu().numpy(), ref["acc"], f"workload {cfg} {L.name} raw")
 
