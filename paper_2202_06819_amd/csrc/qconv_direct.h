@@ -40,8 +40,9 @@ struct DirectEpilogue {   // what the epilogue helpers read, of one job
     uint8_t *yptr;
 };
 
-// f32 results of this wave round toward minus infinity from here on (the
-// requantiser's are its only ones).
+// f32 results of this wave round toward minus infinity from here on.  The
+// requantiser's have to be its only ones: no division by a run-time value, which
+// the compiler works out through f32 reciprocals and conversions.
 __device__ __forceinline__ void round_down_f32() {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2" : : : "memory");
@@ -548,14 +549,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
             return;
         }
         // ---- the waves of a tile add their sums: unit (run b, fragment tn)
-        // belongs to wave unit % wd; the others leave theirs in LDS
+        // belongs to wave unit % wd (a power of two); the others leave theirs in LDS
         constexpr int UNITS = NBK * FP;
+        const int owner = a.wd - 1;
         auto slot = [&](int unit, int d) {   // wave d's sums of a unit
             return smem + (size_t)((unit * a.wd + d) * FE) * 1024 + lane * 16;
         };
 #pragma unroll
         for (int unit = 0; unit < UNITS; ++unit) {
-            if (unit % a.wd == wd_i) continue;
+            if ((unit & owner) == wd_i) continue;
             uint8_t *p = slot(unit, wd_i);
 #pragma unroll
             for (int f = 0; f < FE; ++f) *reinterpret_cast<v4i *>(p + f * 1024) = acc[unit / FP][unit % FP][f];
@@ -563,7 +565,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         __syncthreads();
 #pragma unroll
         for (int unit = 0; unit < UNITS; ++unit) {
-            if (unit % a.wd != wd_i) continue;
+            if ((unit & owner) != wd_i) continue;
             v4i sum[1][FE];
             uint32_t rw[1][NWD];
             load_residual(rw, mt * (FP * 16) + (unit % FP) * 16, chan[unit / FP]);

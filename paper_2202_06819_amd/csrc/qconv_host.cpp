@@ -772,7 +772,7 @@ int auto_xcd_order(const qconv_layout_info &li, const Plan &pl, int64_t filter_b
 // pairs, 16-pixel fragments), waves per output tile and tiles per workgroup,
 // steps in flight, filters resident in LDS.  np 0: not at all.
 struct DirectChoice {
-    int np = 0, fp = 1, wd = 1, wt = 1, la = 9, resident = 0;
+    int np = 0, fp = 1, wd = 1, wt = 1, la = 9, resident = 0;   // wd: a power of two
 };
 
 bool direct_lin(const qconv_desc *d) {
@@ -834,6 +834,12 @@ constexpr DirectCandidate kDirectCandidates[] = {
     {1, 1, {2, 2, 1, 4, 4, 1}, {3.44f, 0.0f, 0.11f, 0.0779f, 0.0567f, 0.0177f, 1.44f, 0.0f}},
     {1, 1, {2, 2, 1, 8, 4, 1}, {3.77f, 0.0f, 0.279f, 0.0f, 0.0f, 0.0173f, 1.69f, 0.0f}},
 };
+constexpr bool depths_are_powers_of_two() {   // the kernels tell a unit's wave by a mask
+    for (const DirectCandidate &k : kDirectCandidates)
+        if (k.c.wd < 1 || (k.c.wd & (k.c.wd - 1)) != 0) return false;
+    return true;
+}
+static_assert(depths_are_powers_of_two());
 // us of a wide launch: base, stage, MFMA, band, epilogue, MB, filter MB, any-size filter, split, shared SIMD, MFMA of one wave
 constexpr float kWideCost[2][11] = {
     {2.91f, 0.769f, 0.0052f, 0.195f, 0.0713f, 0.0f, 0.247f, 0.00736f, 2.11f, 0.0254f, 0.00517f},
