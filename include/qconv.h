@@ -566,8 +566,8 @@ int qconv_last_launch(int64_t *grid, int64_t *threads, int64_t *lds_bytes);
 
 /*
  * qconv_last_kernel -- host only: the kernel that launch ran ("" when the
- * thread has launched none), in a buffer of the calling thread that its next
- * convolution call overwrites.  A tile's name (qconv_tile_info.name) for the
+ * thread has launched none), in static memory or in a buffer of the calling
+ * thread that its next qconv_last_kernel overwrites.  A tile's name (qconv_tile_info.name) for the
  * staged and wide kernels, else a direct kernel's:
  *   direct_b<bits>_k<frag_k of the filter image>_f<16-pixel fragments>x<32-channel
  *   pairs per wave>_d<waves sharing a tile's depth>_t<tiles per workgroup>_l<steps

@@ -34,12 +34,22 @@ namespace {
 
 thread_local char g_err[256] = "";
 
-// Geometry and kernel of the calling thread's most recent convolution launch.
-struct LaunchGeometry {
-    int64_t grid = 0, threads = 0, lds = 0;
-    char kernel[96] = "";
+// How a prepared wide layer runs on the direct kernels: wave tile (32-channel
+// pairs, 16-pixel fragments), waves per output tile and tiles per workgroup,
+// steps in flight, filters resident in LDS.  np 0: not at all.
+struct DirectChoice {
+    int np = 0, fp = 1, wd = 1, wt = 1, la = 9, resident = 0;   // wd: a power of two
 };
-thread_local LaunchGeometry g_last_launch;
+
+// Geometry and kernel of the calling thread's most recent convolution launch:
+// a tile, or a direct kernel (whose name is written out when it is asked for).
+struct LaunchRecord {
+    int64_t grid = 0, threads = 0, lds = 0;
+    const char *tile = "";
+    const DirectInstance *direct = nullptr;
+    DirectChoice choice;
+};
+thread_local LaunchRecord g_last_launch;
 
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 int fail(int code, const char *fmt, ...) {
@@ -768,13 +778,6 @@ int auto_xcd_order(const qconv_layout_info &li, const Plan &pl, int64_t filter_b
     return channel_major < pixel_major ? 2 : 1;
 }
 
-// How a prepared wide layer runs on the direct kernels: wave tile (32-channel
-// pairs, 16-pixel fragments), waves per output tile and tiles per workgroup,
-// steps in flight, filters resident in LDS.  np 0: not at all.
-struct DirectChoice {
-    int np = 0, fp = 1, wd = 1, wt = 1, la = 9, resident = 0;   // wd: a power of two
-};
-
 bool direct_lin(const qconv_desc *d) {
     return d->r == 1 && d->s == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 && d->pad_w == 0;
 }
@@ -941,13 +944,6 @@ DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, con
     // (it rides on staged pixels): 20 % against about 35 % at batch 16.
     const double margin = (lin ? 1.1 : 1.15 + 0.01 * best_us) * (proj ? 1.15 : 1.0);
     return best && best_us * margin < wide_estimate(d, t, pl, z, lin) ? best->c : none;
-}
-
-// The name of a direct launch, as qconv_last_kernel documents it.
-void name_direct(const DirectChoice &c, const DirectInstance &i, char *out, size_t size) {
-    snprintf(out, size, "direct_b%d_k%d_f%dx%d_d%d_t%d_l%d_%s%s%s%s%s", i.bits, i.fkb, c.fp, c.np, c.wd, c.wt, c.la,
-             c.resident ? "resident" : "depth", i.lin ? "_1x1" : "", i.two_steps ? "_two" : "", i.multi ? "_rounds" : "",
-             i.ext ? "_ext" : "");
 }
 
 // One job of a direct launch (its epilogue comes later): filter r x s with
@@ -1283,10 +1279,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
             if (rc) return rc;
             hipError_t e = dl.inst->launch(da, dim3((unsigned)dl.grid), dl.threads, (size_t)dl.lds, (hipStream_t)stream);
             if (e != hipSuccess) return fail(QCONV_EHIP, "conv launch (%s): %s", te.info.name, hipGetErrorString(e));
-            g_last_launch.grid = dl.grid;
-            g_last_launch.threads = dl.threads;
-            g_last_launch.lds = dl.lds;
-            name_direct(dc, *dl.inst, g_last_launch.kernel, sizeof(g_last_launch.kernel));
+            g_last_launch = {dl.grid, dl.threads, dl.lds, "", dl.inst, dc};
             return QCONV_OK;
         }
     }
@@ -1342,10 +1335,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
     if (rc) return rc;
     hipError_t e = launch(a, dim3((unsigned)pl.grid), (size_t)pl.lds, (hipStream_t)stream);
     if (e != hipSuccess) return fail(QCONV_EHIP, "conv launch (%s): %s", te.info.name, hipGetErrorString(e));
-    g_last_launch.grid = pl.grid;
-    g_last_launch.threads = te.info.threads;
-    g_last_launch.lds = pl.lds;
-    snprintf(g_last_launch.kernel, sizeof(g_last_launch.kernel), "%s", te.info.name);
+    g_last_launch = {pl.grid, te.info.threads, pl.lds, te.info.name, nullptr, DirectChoice()};
     return QCONV_OK;
 }
 
@@ -1691,7 +1681,16 @@ int qconv_last_launch(int64_t *grid, int64_t *threads, int64_t *lds_bytes) {
     return g_last_launch.grid > 0 ? QCONV_OK : fail(QCONV_EINVAL, "no convolution launched on this thread yet");
 }
 
-const char *qconv_last_kernel(void) { return g_last_launch.kernel; }
+const char *qconv_last_kernel(void) {
+    const DirectInstance *i = g_last_launch.direct;
+    if (!i) return g_last_launch.tile;
+    const DirectChoice &c = g_last_launch.choice;
+    static thread_local char name[96];
+    snprintf(name, sizeof(name), "direct_b%d_k%d_f%dx%d_d%d_t%d_l%d_%s%s%s%s%s", i->bits, i->fkb, c.fp, c.np, c.wd, c.wt,
+             c.la, c.resident ? "resident" : "depth", i->lin ? "_1x1" : "", i->two_steps ? "_two" : "",
+             i->multi ? "_rounds" : "", i->ext ? "_ext" : "");
+    return name;
+}
 
 int qconv_probe_launch(int32_t blocks, int32_t threads, int32_t lds_bytes, void *stream) {
     g_err[0] = 0;
