@@ -49,6 +49,13 @@ __device__ __forceinline__ void round_down_f32() {
 #endif
 }
 
+// |v| <= room (room < 2^31), for every v: the sum is formed in unsigned, where it
+// may wrap.
+__host__ __device__ constexpr bool within(int32_t v, uint32_t room) { return (uint32_t)v + room <= 2u * room; }
+static_assert(within(1 << 24, 1u << 24) && within(-(1 << 24), 1u << 24) && !within((1 << 24) + 1, 1u << 24) &&
+              !within(-(1 << 24) - 1, 1u << 24) && !within(INT32_MAX, 1u << 24) && !within(INT32_MIN, 1u << 24) &&
+              within(0, 0u) && !within(1, 0u) && !within(-1, 0u));
+
 // Byte N of w = floor(x) saturated to [0, 255] (N = 0 starts a word).
 template <int N>
 __device__ __forceinline__ uint32_t pack_u8(float x, uint32_t w) {
@@ -385,8 +392,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) c
         for (int b = 0; b < NBK; ++b)
 #pragma unroll
             for (int i = 0; i < 4 * FE; ++i) {
-                ok = ok && (uint32_t)(mult[b][i] + (1 << 24)) <= (2u << 24);
-                if constexpr (EXT) ok = ok && (uint32_t)bias[b][i] + room <= 2u * room;
+                ok = ok && within(mult[b][i], 1u << 24);
+                if constexpr (EXT) ok = ok && within(bias[b][i], room);
             }
         f32 = __all(ok);
         if (!f32) return;

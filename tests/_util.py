@@ -180,7 +180,7 @@ def packed_values(y, bits):
 
 def epilogue_forms(g, k, bits, spread, y_shape):
     """(name, arguments) of the epilogues: both output ranges, a clamp inside
-    one, multipliers past 24 bits, extreme shifts, and biases and residuals of
+    one, multipliers about and past 24 bits, extreme shifts, and biases and residuals of
     either signedness."""
     mult = g.integers(1 << 14, 1 << 15, size=k).astype(np.int32)
     span = 8 if bits == 4 else 64
@@ -196,6 +196,12 @@ def epilogue_forms(g, k, bits, spread, y_shape):
         ("inside a range", dict(mult=mult, shift=sh, clamp=(1, 6))),
         ("wide multipliers", dict(mult=(mult.astype(np.int64) * 40000).clip(max=2 ** 31 - 1).astype(np.int32),
                                   shift=min(sh + 15, 62), clamp=full)),
+        # (on both sides of what the f32 form takes, and where a 32-bit sum with its bound would wrap)
+        ("extreme multipliers", dict(mult=np.resize(np.array([2 ** 31 - 1, -2 ** 31, 1 << 24, (1 << 24) + 1, -(1 << 24),
+                                                              -(1 << 24) - 1, 2 ** 31 - (1 << 24)], np.int32), k),
+                                     shift=min(sh + 12, 62), clamp=other)),
+        ("24-bit multipliers", dict(mult=np.resize(np.array([1 << 24, -(1 << 24), (1 << 24) - 1], np.int32), k),
+                                    shift=min(sh + 9, 62), clamp=other)),
         ("shift 1", dict(mult=np.ones(k, np.int32), shift=1, clamp=other)),
         ("shift 62", dict(mult=mult, shift=62, clamp=full)),
         ("bias", dict(mult=mult, shift=sh, clamp=full, bias=g.integers(-300, 300, size=k).astype(np.int32))),
