@@ -794,8 +794,8 @@ bool direct_two_steps(const qconv_desc *d, const DirectChoice &c) {
 // where their best estimate is clearly lower.  The coefficients are least-squares
 // fits to about 1,210 random layers (1x1 to 5x5, strides 1 and 2, 16 to 2048
 // channels, 7 to 112 pixels a side, batch 1 to 256, both widths), each timed
-// with every wave tile and with the wide tile a caller would take; the
-// estimates' errors are 12-17 %.  What they say: a wide launch pays 0.5-0.75 us
+// with every wave tile and with the wide tile a caller would take; their errors
+// on those layers are 12-17 % (direct_margin covers them).  What they say: a wide launch pays 0.5-0.75 us
 // for every stage its workgroups walk in turn, a direct one 0.05-0.3 us for each
 // step of its waves, but loads every operand of every step through the L1, so
 // that few stages and much work favour the wide kernels.
@@ -875,9 +875,17 @@ double wide_estimate(const qconv_desc *d, const qconv_tile_info &t, const Plan &
     return us;
 }
 
-double direct_estimate(const qconv_desc *d, int64_t m, const RouteSizes &z, const DirectCandidate &k) {
+// Wave tiles along the channels of a layer of k: the pairs of whole image blocks
+// (the lanes of a pair of a 4-fragment block hold 8 of every 16 channels, so
+// that a partial block needs both of its pairs), np to a tile.
+int64_t direct_kblocks(int32_t k, int frag_k, int np) {
+    const int64_t pairs = (int64_t)(k + 16 * frag_k - 1) / (16 * frag_k) * (frag_k / 2);
+    return (pairs + np - 1) / np;
+}
+
+double direct_estimate(const qconv_desc *d, int64_t m, int frag_k, const RouteSizes &z, const DirectCandidate &k) {
     const DirectChoice &c = k.c;
-    const int64_t kb = (d->k + 32 * c.np - 1) / (32 * c.np), mt = (m + 16 * c.fp - 1) / (16 * c.fp);
+    const int64_t kb = direct_kblocks(d->k, frag_k, c.np), mt = (m + 16 * c.fp - 1) / (16 * c.fp);
     const int64_t s = (z.steps + c.wd - 1) / c.wd, sr = (s + c.la - 1) / c.la * c.la;
     double f[8] = {1.0};
     if (c.resident) {
@@ -923,8 +931,30 @@ bool direct_fits(const qconv_desc *d, const DirectCandidate &k, int64_t steps, b
 
 int64_t direct_steps(const qconv_desc *d) { return (int64_t)d->r * d->s * ((d->c + 63) / 64); }
 
+// How far below the wide kernel's estimate a direct one has to be.  The margins
+// cover the estimates' errors and were set on 15,100 further random layers timed
+// on both routes (profiles/direct_route_check.md has the same count on others).
+// Past 1.15 + us / 100 for every larger filter and 1.1 for every 1x1,
+//   - 3x3 layers, where the wide kernels have fixed-size instances, by depth in more
+//     than 2048 waves (two a SIMD, the rest waiting) or resident: the estimates
+//     miss part of their L1 traffic;
+//   - 1x1 in the wave tile of four fragments with a bias or a residual: its
+//     registers spill (8-bit: up to 63)
+// ask for more.  With these and the cost of raw sums below, direct launches slower
+// by more than 2 % went from 92 of 8,808 to 45 of 8,494, by more than 10 % from 30
+// to 7, the worst from 1.27x to 1.18x; the 314 layers it cost took 0.82 times the
+// wide kernels' time.  A projection costs a wide launch less than a direct one
+// (it rides on staged pixels): 20 % against about 35 % at batch 16.
+double direct_margin(const qconv_desc *d, const DirectCandidate &k, double us, int64_t waves, bool ext, bool proj) {
+    double margin = k.lin ? 1.1 : 1.15 + 0.01 * us;
+    if (k.lin && k.c.resident && k.c.fp == 4 && ext) margin = 1.25;
+    if (d->r == 3 && d->s == 3 && k.c.resident) margin = 1.3 + 0.01 * us;
+    if (d->r == 3 && d->s == 3 && !k.c.resident && waves > 2 * kNumCUs * 4) margin = std::max(margin, 1.4);
+    return margin * (proj ? 1.15 : 1.0);
+}
+
 DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_tile_info &t, const Plan &pl,
-                           int64_t filter_bytes, bool proj) {
+                           int64_t filter_bytes, bool raw, bool ext, bool proj) {
     const int lin = direct_lin(d) ? 1 : 0;
     const RouteSizes z{li.x_bytes / 1e6, li.y_packed_bytes / 1e6, filter_bytes / 1e6, d->bits / 8.0, direct_steps(d)};
     const DirectChoice none;
@@ -932,18 +962,21 @@ DirectChoice choose_direct(const qconv_desc *d, const qconv_layout_info &li, con
     double best_us = 1e30;
     for (const DirectCandidate &k : kDirectCandidates) {
         if (!direct_fits(d, k, z.steps, proj)) continue;
-        const double us = direct_estimate(d, li.m, z, k);
+        const double us = direct_estimate(d, li.m, t.frag_k, z, k);
         if (us < best_us) {
             best_us = us;
             best = &k;
         }
     }
-    // The margin covers the estimates' errors; long launches of larger filters
-    // are where a wrong choice costs most (up to 1.6x) and the wide kernels are
-    // at their best.  A projection costs a wide launch less than a direct one
-    // (it rides on staged pixels): 20 % against about 35 % at batch 16.
-    const double margin = (lin ? 1.1 : 1.15 + 0.01 * best_us) * (proj ? 1.15 : 1.0);
-    return best && best_us * margin < wide_estimate(d, t, pl, z, lin) ? best->c : none;
+    if (!best) return none;
+    // raw sums: about 0.2 us a MB past the packed output's, a little more from the
+    // resident 1x1 kernels, whose lanes store 8 or 16 channels each
+    const double raw_mb = raw ? (li.y_raw_bytes - li.y_packed_bytes) / 1e6 : 0.0;
+    const double us = best_us + (lin && best->c.resident ? 0.23 : 0.2) * raw_mb;
+    const double wide_us = wide_estimate(d, t, pl, z, lin) + 0.2 * raw_mb;
+    const int64_t waves = direct_kblocks(d->k, t.frag_k, best->c.np) *
+                          ((li.m + 16 * best->c.fp - 1) / (16 * best->c.fp)) * best->c.wd;
+    return us * direct_margin(d, *best, us, waves, ext, proj) < wide_us ? best->c : none;
 }
 
 // One job of a direct launch (its epilogue comes later): filter r x s with
@@ -1002,8 +1035,7 @@ bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_t
     a.kt_stride = (int32_t)((d->c + t.chunk_c - 1) / t.chunk_c * (t.chunk_c / 16) * pl.pstride_w);
     a.wk = t.waves_k;
     a.pairs = (int32_t)(pl.ktiles * t.tile_k / 32);
-    const int need_pairs = (d->k + 16 * t.frag_k - 1) / (16 * t.frag_k) * (t.frag_k / 2);   // a block holds frag_k / 2 pairs
-    a.kblocks = (need_pairs + c.np - 1) / c.np;
+    a.kblocks = (int32_t)direct_kblocks(d->k, t.frag_k, c.np);
     a.mtiles = (a.m + 16 * c.fp - 1) / (16 * c.fp);
     a.tiles = a.kblocks * a.mtiles;
     a.wd = c.wd;
@@ -1257,7 +1289,7 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
         DirectArgs da;
         DirectLaunch dl;
         const bool fits = form < 0 || direct_fits(d, kDirectCandidates[form], direct_steps(d), proj);
-        const DirectChoice dc = form < 0 ? choose_direct(d, li, te.info, pl, wb, proj)
+        const DirectChoice dc = form < 0 ? choose_direct(d, li, te.info, pl, wb, !requant, ext, proj)
                                          : fits ? kDirectCandidates[form].c : DirectChoice();
         if (plan_direct(d, li, te.info, pl, ext, wb, x, w, proj, dc, da, dl)) {
             da.mode = requant ? QCONV_OUT_REQUANT : QCONV_OUT_RAW_I32;

@@ -110,6 +110,27 @@ def test_last_kernel_names_what_ran():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("n,h,w,c,k,stride,bits,tile", [
+    (5, 83, 92, 1024, 24, 1, 8, "wide_b8_w4x1_f2x4_c64"),    # 58 us on its tile, 101 direct
+    (28, 32, 41, 384, 24, 1, 8, "wide_b8_w4x1_f2x4_c64"),    # 23, 36
+    (62, 63, 72, 128, 32, 2, 4, "wide_b4_w8x1_f1x4_c64"),    # 15, 26
+])
+def test_partial_blocks_are_priced(n, h, w, c, k, stride, bits, tile):
+    """Few output channels from a 4-fragment image: the direct kernels compute
+    the block's other channels too, so that these stay on their tile's kernel."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    dev = torch.device("cuda:0")
+    d = qi.Layer("partial", n, h, w, c, k, 3, 3, stride, 1, bits, bits == 8, True).desc()
+    x = torch.zeros(q.layout(d)["x_bytes"], dtype=torch.uint8, device=dev)
+    tid = next(t["id"] for t in q.tiles() if t["name"] == tile)
+    announce(f"partial blocks {n}x{h}x{w} {c}->{k} {tile}")
+    q.conv2d(d, x, torch.zeros(q.prepared_filter_bytes(d, tid), dtype=torch.uint8, device=dev), tile=tid, prepared=True)
+    torch.cuda.synchronize()
+    assert q.last_kernel() == tile
+
+
 def _full_splits(q, d, tile):
     """Split factors above one that leave no split empty."""
     chunks = q.max_splits(d, tile)
