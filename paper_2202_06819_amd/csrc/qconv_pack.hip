@@ -8,17 +8,25 @@
 // bytes per lane, two lanes per 64-byte row segment), saturates every value into
 // the target range and parks it in LDS; it then reads 8 channels x 4 pixels per
 // lane as dwords, transposes the bytes in registers, packs nibbles and writes
-// each pixel's words.  The LDS row pitch is 17 dwords, odd, so that the channels
-// of a column lie in different banks.
+// each pixel's words.  The LDS row pitch is 17 dwords: the dwords a wave of a
+// 64-channel tile reads at once (8 channel groups 136 dwords apart, 8 pixel
+// quads) lie in 64 banks, those of a 128-channel tile (16 groups, 4 quads) in 32,
+// two to a bank.
 //
 // The kernel is HBM-bound: every input byte is read once and every output byte
-// written once.  Up to 64 channels PK_C is 64, which wastes no rows and gives a
-// batch-8 56x56 tensor more than twice as many workgroups as there are CUs.
-// Above 64 channels it is 128: a pixel's packed words are then written in 64-byte
-// runs (4-bit) instead of 32-byte ones, 41x768x59x62 29.5 us (5.9 TB/s) against
-// 32.7 us in 64-channel tiles, 64x256x56x56 13.6 against 13.8 us.  Rows of any
-// length are read with 16-byte loads, unaligned where the row is: those rows of
-// 3658 bytes took 236 us with byte loads.
+// written once.  PK_C is 64, except where 128 pays: the channels fill whole pairs of
+// 64-channel tiles, so that no more rows are staged, and 2048 workgroups or more
+// are left.  A pixel's packed words are then written in 64-byte runs (4-bit)
+// instead of 32-byte ones: 41x256x108x108 32.8 against 37.6 us, 41x128x108x108
+// 17.1 against 18.2, 64x2048x28x28 27.2 against 27.4.  With a half-empty tile it
+// costs more than it gives (41x160x108x108 27.0 against 23.9, 41x192x108x108 28.4
+// against 26.6), and on small tensors the larger workgroups take up to 0.2 us
+// longer (16x192x1x1 2.9 against 2.8, 16x96x56x56 4.1 against 3.9).
+//
+// Rows of 11 pixels or more are read with 16-byte loads, unaligned where the row is:
+// 41x256x108x109 33 us, with byte loads 199.  Shorter ones (filters, 1x1 images)
+// are read byte by byte, which moves less: 1024x2048x1x1 24.0 against 29.2 us,
+// 1024x256x3x3 6.2 against 6.5; at 12 pixels it is 6.8 against 6.3.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,7 +35,8 @@
 namespace qconv {
 
 constexpr int PK_P = 64;          // pixels per tile (64-byte segments of each channel row)
-constexpr int PK_PITCH = 68;      // LDS row pitch in bytes (17 dwords: conflict-free column reads)
+constexpr int PK_PITCH = 68;      // LDS row pitch in bytes
+constexpr int PK_SHORT = 11;      // rows below so many pixels are read by bytes
 
 // Same renumbering as the convolution kernels: block b runs on XCD b % 8;
 // give every XCD a contiguous range so neighbouring pixel tiles (which share
@@ -69,7 +78,7 @@ __global__ void __launch_bounds__(2 * PK_C)
     const size_t obase = (size_t)ig * hw * nb.d + (img - ig * (int)nb.d);
     auto out_pixel = [&](int px) { return obase + (size_t)px * nb.d; };
 
-    // ---- phase 1: 64 channel rows x 64 pixels; a lane reads 32 consecutive
+    // ---- phase 1: PK_C channel rows x 64 pixels; a lane reads 32 consecutive
     // pixels of one row, saturates them and parks them in LDS
     {
         const int row = tid >> 1;
@@ -77,7 +86,7 @@ __global__ void __launch_bounds__(2 * PK_C)
         const int ch = c0 + row;
         uint32_t v[8];
         const int8_t *rp = plane + (size_t)ch * hw + p0 + seg;
-        if (ch < c && p0 + seg < hw && rp + 32 <= end) {
+        if (ch < c && hw >= PK_SHORT && p0 + seg < hw && rp + 32 <= end) {
             // (rows of any length: the loads are unaligned where the row is, and
             // those past a row's end read the next row, whose pixels are not stored)
             uint4 a, b;
@@ -86,7 +95,7 @@ __global__ void __launch_bounds__(2 * PK_C)
             v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
             v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
         } else {
-            // the tensor's last bytes
+            // short rows, and the tensor's last bytes
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 uint32_t w = 0;
@@ -160,7 +169,9 @@ hipError_t launch_pack(const int8_t *src, void *dst, int32_t n, int32_t c, int32
                        int32_t is_signed, int32_t nb, hipStream_t stream) {
     const int hw = h * w;
     const int ptiles = (hw + PK_P - 1) / PK_P;
-    const int pkc = c > 64 ? 128 : 64;
+    const int c64 = (c + 63) / 64;
+    const bool wide = c64 % 2 == 0 && (long long)n * ptiles * (c64 / 2) >= 2048;   // (see the top)
+    const int pkc = wide ? 128 : 64;
     const int ctiles = (c + pkc - 1) / pkc;
     const long long blocks = (long long)n * ptiles * ctiles;
     uint8_t *d = static_cast<uint8_t *>(dst);

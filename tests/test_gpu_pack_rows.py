@@ -1,5 +1,7 @@
 """The pack kernel's loads: rows that start at every byte alignment, sources that
-do not start on a word, and the tensor's last bytes, against the oracle."""
+do not start on a word, the tensor's last bytes, rows on both sides of what is
+read by bytes and tensors on both sides of what takes 128-channel tiles, against
+the oracle; and the largest grid of 64-channel tiles."""
 import numpy as np
 import pytest
 
@@ -10,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,c,h,w", [(1, 8, 1, 31), (2, 8, 1, 33), (1, 64, 5, 7), (3, 72, 7, 9), (1, 136, 1, 129),
-                                     (2, 16, 13, 5), (1, 8, 1, 1)])
+                                     (2, 16, 13, 5), (1, 8, 1, 1), (5, 200, 3, 3), (5, 200, 2, 5), (5, 200, 1, 11),
+                                     (60, 256, 29, 33), (72, 256, 29, 33), (140, 160, 23, 21)])
 @pytest.mark.parametrize("bits,signed", [(4, False), (4, True), (8, True)])
 def test_pack_unaligned_rows(n, c, h, w, bits, signed):
     import torch
@@ -27,3 +30,17 @@ def test_pack_unaligned_rows(n, c, h, w, bits, signed):
         y = q.pack(src, bits, signed)
         torch.cuda.synchronize()
         assert_same(y.cpu().numpy(), want, f"pack {n}x{c}x{h}x{w} {bits} {shift}")
+
+
+def test_pack_of_the_largest_grid():
+    """A launch holds fewer than 2^32 threads: nine million one-pixel images of 132
+    channels are 27 million workgroups of 128.  One pixel an image, the packed
+    layout is the source's."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    x = torch.randint(-128, 128, (9_000_000, 132, 1, 1), dtype=torch.int8, device="cuda:0")
+    announce("pack 9000000x132x1x1 8-bit")
+    y = q.pack(x, 8, True)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(-1), x.view(-1))
