@@ -5,7 +5,10 @@ compiled gfx950 tile space).
 For each convolution shape and every compiled tile that can run it:
   1. run it and check that its output bytes equal those of a reference tile
      (integer sums have one value, so every tile must agree);
-  2. time it with HIP events over back-to-back launches (median of rounds);
+  2. time it with HIP events over back-to-back launches (median of rounds) and
+     note the kernel that ran: without a split the library may take a direct
+     kernel, the same one from several tiles' filter images, which is timed once,
+     and the tile's own kernel beside it (``tile_us``);
   3. append one JSON line to the results file (the run is resumable: pairs
      already in the file are skipped).
 The fastest tile per shape goes into the tuned table that qconv2d callers use
@@ -126,6 +129,18 @@ def _time(make_call, reps: int, rounds: int) -> float:
     return statistics.median(res)
 
 
+def _launch_row(kernel: str, call_us, tile_us, direct: dict) -> dict:
+    """The timing of one candidate that ran `kernel`: a direct kernel's time is
+    measured for its first candidate (kept in `direct`) and shared by the others,
+    which would only time it again, with the time of the tile's own kernel
+    beside it."""
+    if not kernel.startswith("direct_"):
+        return {"kernel": kernel, "us": round(call_us(), 3)}
+    if kernel not in direct:
+        direct[kernel] = round(call_us(), 3)
+    return {"kernel": kernel, "us": direct[kernel], "tile_us": round(tile_us(), 3)}
+
+
 def sweep_layer(d: dict, x: torch.Tensor, w: torch.Tensor, mult: torch.Tensor | None, *, shift=20, relu=True,
                 clamp=(0, 15), reps=100, rounds=5, done=frozenset(), log=print,
                 expected: torch.Tensor | None = None) -> list[dict]:
@@ -143,7 +158,7 @@ def sweep_layer(d: dict, x: torch.Tensor, w: torch.Tensor, mult: torch.Tensor | 
         ref = ref_call().clone()   # packed filters, default tile
     else:
         ref = expected.to(x.device)
-    rows = []
+    rows, direct = [], {}
     for t in qconv.tiles():
         if qconv.tile_status(d, t["id"]) != 0:
             continue
@@ -153,18 +168,20 @@ def sweep_layer(d: dict, x: torch.Tensor, w: torch.Tensor, mult: torch.Tensor | 
                 continue
             ws = qconv.make_workspace(d, t["id"], splits, x.device)
 
-            def make(stream=None, tid=t["id"], splits=splits, ws=ws):
+            def make(stream=None, tid=t["id"], splits=splits, ws=ws, form=None):
                 return qconv.Conv2dCall(d, x, wprep, requant=requant, mult=mult, shift=shift, relu=relu,
                                         clamp=clamp, tile=tid, prepared=True, splits=splits, workspace=ws,
-                                        stream=stream)
+                                        stream=stream, form=form)
 
             out = make()()
+            kernel = qconv.last_kernel()
             torch.cuda.synchronize()
             same = out.shape == ref.shape and bool(torch.equal(out.view(ref.dtype), ref))
-            us = _time(make, reps, rounds)
-            tops = ops / (us * 1e-6) / 1e12
+            timing = _launch_row(kernel, lambda: _time(make, reps, rounds),
+                                 lambda: _time(lambda stream: make(stream, form=-1), reps, rounds), direct)
+            tops = ops / (timing["us"] * 1e-6) / 1e12
             row = {"shape": key, "tile": t["name"], "tile_id": t["id"], "splits": splits,
-                   "default": t["id"] == default and splits == 1, "us": round(us, 3), "tops": round(tops, 2),
+                   "default": t["id"] == default and splits == 1, **timing, "tops": round(tops, 2),
                    "pct_int8_peak": round(100 * tops / INT8_PEAK_TOPS, 3), "identical": same}
             rows.append(row)
             log(json.dumps(row))
@@ -187,15 +204,15 @@ def sweep_proj_layer(d: dict, x: torch.Tensor, w3: torch.Tensor, w1: torch.Tenso
     kw = dict(requant=True, mult=mult, shift=shift, relu=relu, clamp=clamp,
               proj=dict(mult=mult2, shift=shift2, relu=relu2, clamp=clamp)) if requant else {}
 
-    def make_for(tid, wprep, stream=None, splits=1, ws=None):
-        return qconv.ProjConv2dCall(d, x, wprep, tile=tid, stream=stream, splits=splits, workspace=ws, **kw)
+    def make_for(tid, wprep, stream=None, splits=1, ws=None, form=None):
+        return qconv.ProjConv2dCall(d, x, wprep, tile=tid, stream=stream, splits=splits, workspace=ws, form=form, **kw)
 
     if expected is None:
         y, yp = make_for(default, qconv.prepare_filters_proj(d, w3, w1, default))()
         ref = (y.clone(), yp.clone())
     else:
         ref = tuple(e.to(x.device) for e in expected)
-    rows = []
+    rows, direct = [], {}
     for t in qconv.tiles():
         if qconv.proj_tile_status(d, t["id"]) != 0:
             continue
@@ -208,13 +225,15 @@ def sweep_proj_layer(d: dict, x: torch.Tensor, w3: torch.Tensor, w1: torch.Tenso
             nws = qconv.proj_workspace_bytes(d, t["id"], splits)
             ws = torch.zeros(nws, dtype=torch.uint8, device=x.device) if nws else None
             y, yp = make_for(t["id"], wprep, splits=splits, ws=ws)()
+            kernel = qconv.last_kernel()
             torch.cuda.synchronize()
             same = all(o.shape == r.shape and bool(torch.equal(o.view(r.dtype), r)) for o, r in zip((y, yp), ref))
-            us = _time(lambda stream, tid=t["id"], wprep=wprep, splits=splits, ws=ws:
-                       make_for(tid, wprep, stream, splits, ws), reps, rounds)
-            tops = ops / (us * 1e-6) / 1e12
+            timing = _launch_row(
+                kernel, lambda: _time(lambda stream: make_for(t["id"], wprep, stream, splits, ws), reps, rounds),
+                lambda: _time(lambda stream: make_for(t["id"], wprep, stream, form=-1), reps, rounds), direct)
+            tops = ops / (timing["us"] * 1e-6) / 1e12
             row = {"shape": key, "tile": t["name"], "tile_id": t["id"], "splits": splits,
-                   "default": t["id"] == default and splits == 1, "us": round(us, 3), "tops": round(tops, 2),
+                   "default": t["id"] == default and splits == 1, **timing, "tops": round(tops, 2),
                    "pct_int8_peak": round(100 * tops / INT8_PEAK_TOPS, 3), "identical": same}
             rows.append(row)
             log(json.dumps(row))

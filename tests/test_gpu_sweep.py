@@ -19,6 +19,19 @@ SHAPES = [
 ]
 
 
+def _check_kernels(rows):
+    """Each row names the kernel it timed: the tile's, always where there is a
+    split, or a direct one, timed once and with the tile's own time beside it."""
+    shared = {}
+    for r in rows:
+        if r["kernel"].startswith("direct_"):
+            assert r["splits"] == 1 and r["tile_us"] > 0
+            assert shared.setdefault(r["kernel"], r["us"]) == r["us"]
+        else:
+            assert r["kernel"] == r["tile"] and "tile_us" not in r
+    return len(shared)
+
+
 @pytest.mark.parametrize("lid", range(len(SHAPES)), ids=[L.name for L in SHAPES])
 def test_sweep_candidates_match_the_oracle(lid):
     import torch
@@ -45,6 +58,7 @@ def test_sweep_candidates_match_the_oracle(lid):
     assert {(r["tile"], r["splits"]) for r in rows} == want_rows and len(rows) == len(want_rows)
     assert all(r["identical"] for r in rows)
     assert any(r["splits"] > 1 for r in rows) == any(sp > 1 for _, sp in want_rows)
+    assert _check_kernels(rows) >= 1, "no candidate of these small layers took a direct kernel"
     best = sweep.best_per_shape(rows)[sweep.shape_key(d, requant)]
     assert best["us"] == min(r["us"] for r in rows)
 
@@ -72,3 +86,4 @@ def test_proj_sweep_candidates_match_the_oracle():
     want = {tt["name"] for tt in qconv.tiles() if qconv.proj_tile_status(L.desc(), tt["id"]) == 0}
     assert {r["tile"] for r in rows} == want and len(rows) == len(want) >= 2
     assert all(r["identical"] for r in rows)
+    assert _check_kernels(rows) >= 1
