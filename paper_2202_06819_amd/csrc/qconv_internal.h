@@ -35,6 +35,16 @@ __host__ __device__ inline uint32_t fdiv(uint32_t n, FastDiv f) {
     return (t + n) >> f.shr;
 }
 
+// Launches of at most 2^31 threads that cover `blocks` workgroups: a launch's
+// threads are counted in 32 bits, and one of 2^32 or more runs the remainder
+// only, without an error.  go(first workgroup, count).
+template <class Launch>
+void launch_slices(long long blocks, int threads, Launch go) {
+    const long long most = (1ll << 31) / threads;
+    for (long long first = 0; first < blocks; first += most)
+        go(first, (unsigned)(blocks - first < most ? blocks - first : most));
+}
+
 // The f32 requantiser of an epilogue (EpiParams in qconv_device.h); kind 0: not
 // used (the clamp is not a whole output range, or an accumulator may pass 2^24).
 struct FloatEpilogue {

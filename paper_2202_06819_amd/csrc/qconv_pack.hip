@@ -55,16 +55,16 @@ __device__ __forceinline__ uint32_t gather_byte(const uint32_t (&t)[4], int j) {
 
 // (ptiles, ctiles, nb: the divisors of the block and image decompositions)
 // PK_C: channels per tile, 2 PK_C threads (phase 2: PK_C / 8 channel groups x 16
-// pixel quads)
+// pixel quads).  This launch's workgroups are those from `first` on of `blocks`.
 template <int BITS, bool SIGNED, int PK_C>
 __global__ void __launch_bounds__(2 * PK_C)
     pack_nchw(const int8_t *__restrict__ src, const int8_t *end, uint8_t *__restrict__ dst, int c, int hw,
-              FastDiv ptiles, FastDiv ctiles, FastDiv nb) {
+              FastDiv ptiles, FastDiv ctiles, FastDiv nb, int first, int blocks) {
     constexpr int LO = SIGNED ? -(1 << (BITS - 1)) : 0;
     constexpr int HI = SIGNED ? (1 << (BITS - 1)) - 1 : (1 << BITS) - 1;
     __shared__ __attribute__((aligned(16))) uint8_t tile[PK_C * PK_PITCH];
     const int tid = threadIdx.x;
-    int bid = pack_xcd_block(blockIdx.x, gridDim.x);
+    int bid = pack_xcd_block(first + (int)blockIdx.x, blocks);
     const int rest = (int)fdiv((uint32_t)bid, ptiles);
     const int pt = bid - rest * (int)ptiles.d;
     const int img = (int)fdiv((uint32_t)rest, ctiles);
@@ -176,10 +176,15 @@ hipError_t launch_pack(const int8_t *src, void *dst, int32_t n, int32_t c, int32
     const long long blocks = (long long)n * ptiles * ctiles;
     uint8_t *d = static_cast<uint8_t *>(dst);
     const int8_t *end = src + (size_t)n * c * hw;
-    const dim3 grid((unsigned)blocks), block(2 * pkc);
+    const dim3 block(2 * pkc);
     const FastDiv dp = make_fastdiv((uint32_t)ptiles), dc = make_fastdiv((uint32_t)ctiles),
                   dn = make_fastdiv((uint32_t)(nb > 0 ? nb : 1));
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, src, end, d, c, hw, dp, dc, dn); };
+    auto go = [&](auto kernel) {
+        launch_slices(blocks, 2 * pkc, [&](long long first, unsigned count) {
+            hipLaunchKernelGGL(kernel, dim3(count), block, 0, stream, src, end, d, c, hw, dp, dc, dn, (int)first,
+                               (int)blocks);
+        });
+    };
     if (pkc == 128) {
         if (bits == 4 && is_signed)
             go(pack_nchw<4, true, 128>);

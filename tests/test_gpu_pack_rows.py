@@ -44,3 +44,36 @@ def test_pack_of_the_largest_grid():
     y = q.pack(x, 8, True)
     torch.cuda.synchronize()
     assert torch.equal(y.view(-1), x.view(-1))
+
+
+def test_pack_beyond_the_largest_launch():
+    """34 million one-pixel images are as many workgroups of 128 threads, more than
+    the 2^32 threads a launch counts: the pack on its own, and the one that
+    qconv2d_packing runs before a convolution of several stages.  One pixel an
+    image, the packed layout is the source's and only the centre taps count."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    n, c, k, shift = 34_000_000, 16, 4, 22
+    d = dict(n=n, h=1, w=1, c=c, k=k, r=3, s=3, stride_h=1, stride_w=1, pad_h=1, pad_w=1, bits=8, x_signed=1, w_signed=1)
+    tile = next(t["id"] for t in q.tiles() if t["variant"] == 2 and q.tile_status(d, t["id"]) == 0)
+    g = torch.Generator(device="cuda:0").manual_seed(93)
+    x = torch.randint(-128, 128, (n, c, 1, 1), dtype=torch.int8, device="cuda:0", generator=g)
+    w = torch.randint(-127, 128, (k, c, 3, 3), dtype=torch.int8, device="cuda:0", generator=g)
+    mult = torch.randint(1 << 14, 1 << 15, (k,), dtype=torch.int32, device="cuda:0", generator=g)
+    announce("pack 34000000x16x1x1 8-bit")
+    y = q.pack(x, 8, True)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(-1), x.view(-1))
+    del y
+    announce("fused pack 34000000x16x1x1 8-bit")
+    call = q.PackingConv2dCall(d, x, q.prepare_filters(d, q.pack(w, 8, True), tile), tile=tile, mult=mult, shift=shift,
+                               relu=False, clamp=(-128, 127), x_packed=True)
+    y = call().view(n, k)
+    torch.cuda.synchronize()
+    assert torch.equal(call.x_packed.view(-1), x.view(-1))
+    centre = w[:, :, 1, 1].double().t().contiguous()
+    for i in range(0, n, 4_000_000):
+        acc = (x[i:i + 4_000_000].view(-1, c).double() @ centre).to(torch.int64)
+        want = ((acc * mult.to(torch.int64) + (1 << (shift - 1))) >> shift).clamp(-128, 127).to(torch.int8)
+        assert torch.equal(y[i:i + 4_000_000], want)
