@@ -257,6 +257,8 @@ struct UnrollArgs {
     // unroll_runs (filled in by launch_unroll)
     FastDiv div_out_h, div_vpp, div_run;
     int32_t pixels_per_round;
+    // a launch's first output row of all n * out_h (filled in by launch_unroll)
+    int32_t first;
 };
 
 // Defined in qconv_unroll.hip.

@@ -42,8 +42,9 @@ __global__ void __launch_bounds__(256) unroll_patches(const int8_t *__restrict__
     }
     const int nrb = a.c * a.taps_h;
     const int vpp = a.c_out / 16;
-    const int u = (int)(blockIdx.x % (unsigned)a.out_h);
-    const int img = (int)(blockIdx.x / (unsigned)a.out_h);
+    const unsigned row = (unsigned)a.first + blockIdx.x;
+    const int u = (int)(row % (unsigned)a.out_h);
+    const int img = (int)(row / (unsigned)a.out_h);
     // staged row rb = ci * taps_h + b holds source row u*stride_h + b - pad_h
     // of channel ci; each thread takes one column of up to 8 rows at a time,
     // so that their loads are in flight together
@@ -104,8 +105,9 @@ __global__ void __launch_bounds__(256) unroll_runs(const int8_t *__restrict__ sr
     const int c = a.c;
     const int run = a.taps_w * c;
     const int row_bytes = (a.lw * c + 3) & ~3;
-    const int img = (int)fdiv(blockIdx.x, a.div_out_h);
-    const int u = (int)blockIdx.x - img * a.out_h;
+    const uint32_t row = (uint32_t)a.first + blockIdx.x;
+    const int img = (int)fdiv(row, a.div_out_h);
+    const int u = (int)row - img * a.out_h;
     const int nrb = c * a.taps_h;
     uint8_t *rows = smem + 16;   // (a window may start up to 15 bytes before its row)
     const int8_t *image = src + (int64_t)img * c * a.h * a.w;
@@ -196,17 +198,22 @@ int64_t unroll_lds_bytes(const UnrollArgs &a) { return 4ll * a.c_out + (int64_t)
 hipError_t launch_unroll(const int8_t *src, int8_t *dst, const UnrollArgs &a, hipStream_t stream) {
     const int64_t blocks = (int64_t)a.n * a.out_h;
     if (blocks == 0 || a.wout == 0) return hipSuccess;
-    if (use_unroll_runs(a)) {
-        UnrollArgs r = a;
+    const bool runs = use_unroll_runs(a);
+    UnrollArgs r = a;
+    if (runs) {
         r.div_out_h = make_fastdiv((uint32_t)a.out_h);
         r.div_vpp = make_fastdiv((uint32_t)(a.c_out / 16));
         r.div_run = make_fastdiv((uint32_t)(a.taps_w * a.c));
         r.pixels_per_round = 256 / (a.c_out / 16);
-        hipLaunchKernelGGL(unroll_runs, dim3((unsigned)blocks), dim3(256), (size_t)unroll_runs_lds(a), stream, src, dst,
-                           r);
-    } else
-        hipLaunchKernelGGL(unroll_patches, dim3((unsigned)blocks), dim3(256), (size_t)unroll_lds_bytes(a), stream, src,
-                           dst, a);
+    }
+    const size_t lds = (size_t)(runs ? unroll_runs_lds(a) : unroll_lds_bytes(a));
+    launch_slices(blocks, 256, [&](long long first, unsigned count) {
+        r.first = (int32_t)first;
+        if (runs)
+            hipLaunchKernelGGL(unroll_runs, dim3(count), dim3(256), lds, stream, src, dst, r);
+        else
+            hipLaunchKernelGGL(unroll_patches, dim3(count), dim3(256), lds, stream, src, dst, r);
+    });
     return hipGetLastError();
 }
 

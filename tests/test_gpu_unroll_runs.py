@@ -32,3 +32,20 @@ def test_unroll_runs(n, c, h, w, c_out, th, sh, ph, tw, sw, pw):
     plan = dict(taps_h=th, stride_h=sh, pad_h=ph, out_h=(h + 2 * ph - th) // sh + 2, taps_w=tw, stride_w=sw, pad_w=pw)
     y = q.unroll(torch.from_numpy(x).to("cuda:0"), c_out, **plan)
     assert np.array_equal(y.cpu().numpy(), unroll_def(x, c_out, **plan))
+
+
+@pytest.mark.parametrize("c,taps_w", [(1, 16), (16, 1), (1, 8)])
+def test_unroll_beyond_the_largest_launch(c, taps_w):
+    """17 million rows are as many workgroups of 256 threads, more than the 2^32
+    threads a launch counts; both kernels.  A row of one pixel unrolls to its own
+    bytes, channels after columns, and zeros."""
+    import torch
+    from paper_2202_06819_amd import qconv as q
+
+    n = 17_000_000
+    announce(f"unroll {n}x{c}x1x{taps_w}")
+    x = torch.randint(-128, 128, (n, c, 1, taps_w), dtype=torch.int8, device="cuda:0")
+    y = q.unroll(x, 16, taps_h=1, stride_h=1, pad_h=0, out_h=1, taps_w=taps_w, stride_w=1, pad_w=0).view(n, 16)
+    torch.cuda.synchronize()
+    real = c * taps_w
+    assert torch.equal(y[:, :real].reshape(-1), x.view(-1)) and not y[:, real:].any()
