@@ -1073,7 +1073,7 @@ bool plan_direct(const qconv_desc *d, const qconv_layout_info &li, const qconv_t
             out.grid *= 2;
         }
     }
-    return out.grid > 0 && out.grid < (1ll << 31);
+    return out.grid > 0 && out.grid * out.threads < (1ll << 32);   // a launch's threads are counted in 32 bits
 }
 
 // The convolution; w is packed KRSC filters (prepared == false) or the

@@ -646,3 +646,16 @@ def test_forms_are_checked_before_anything_runs(q):
         q.Conv2dCall(d, None, None, tile=wide, prepared=True, splits=2, form=0)
     with pytest.raises(q.QConvError):
         q.ProjConv2dCall(d, None, None, tile=wide, splits=2, form=-1)
+
+
+def test_forms_past_the_largest_launch_are_refused(q):
+    """A launch's threads are counted in 32 bits: a million 11x11 images of 4 output
+    channels in 16-pixel tiles of 8 waves are 7.7e9 threads (a pair of channel
+    pairs each), which the tile's persistent kernel walks with a resident grid."""
+    d = D(n=1_000_000, h=11, w=11, c=16, k=4, bits=8, x_signed=1)
+    tile = next(t["id"] for t in q.tiles() if t["name"] == "wide_b8_w1x4_f4x4_c64")
+    assert q.tile_status(d, tile) == q.OK
+    depth8 = 3   # one 16-pixel fragment x one channel pair, 8 waves a tile
+    rc = q.lib().qconv2d_form(ctypes.byref(q.make_desc(d)), 1 << 36, 1 << 34, q.prepared_filter_bytes(d, tile), None,
+                              1 << 38, None, None, tile, depth8, None)
+    assert rc == q.EUNSUPPORTED
