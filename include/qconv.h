@@ -351,13 +351,16 @@ int qconv2d_proj(const qconv_desc *d, const void *x, const void *w_prepared, siz
  * int8 activations and saturates each value into the b-bit range of
  * d->x_signed while it stages its input band, so y is exactly
  * qconv2d_prepared(qconv_pack(x_nchw)).  One launch instead of two, for a
- * network's first layer.
+ * network's first layer; with x_packed given and bands that workgroups would
+ * stage several times over (more than two stages a workgroup, or two with rows of
+ * w % 4 != 0 pixels), qconv_pack into x_packed and then the convolution from it,
+ * on the tile's kernel or a direct one as qconv2d_prepared.
  *   x_nchw    DEVICE int8, n x c x h x w, 16-byte aligned
  *   x_packed  DEVICE, qconv_layout_info.x_bytes, 16-byte aligned, or NULL:
- *             also receives qconv_pack(x_nchw), each pixel written by the
- *             workgroup whose band's rows it starts (needs bands that cover
- *             every input row: stride_h <= r and the last window reaching the
- *             last row, else QCONV_EUNSUPPORTED)
+ *             also receives qconv_pack(x_nchw); in one launch each pixel is
+ *             written by the workgroup whose band's rows it starts (needs bands
+ *             that cover every input row: stride_h <= r and the last window
+ *             reaching the last row, else QCONV_EUNSUPPORTED)
  * Runs a wide tile's 3x3 instance (tile_id as for the prepared filters;
  * d->r == d->s == 3), plain layout, no split, no bias or residual; other
  * requests return QCONV_EUNSUPPORTED.  No operand may overlap another.
