@@ -136,10 +136,17 @@ __device__ __forceinline__ void epilogue_f32(const DirectEpilogue &a, const Floa
 // LIN: a 1x1 filter at stride 1 without padding.  B16 (4 bits): steps come in
 // pairs, 128 channels, and a lane loads the 16 bytes of both at once, 32
 // consecutive channels (its granules are 2 gq and 2 gq + 1); for channels in whole
-// 128s.  (On 3x3 layers it changes little: 14.3 -> 14.7 us at 28x28 128->128 N=64,
-// 21.2 -> 18.0 at 14x14 256->256, where the wide kernels take 13.3 and 11.9.)  The loads, not the arithmetic, bound these kernels: 1x1 256->64 at 56x56
+// 128s.  The loads, not the arithmetic, bound these kernels: 1x1 256->64 at 56x56
 // N=64 takes 9.2 us with them and 12.1 with 8-byte loads, 2048->512 at 7x7 9.6 and
-// 12.6.
+// 12.6.  3x3 filters keep one step a load: with two, 28x28 128->128 N=64 went from
+// 14.3 to 14.7 us and 14x14 256->256 from 21.2 to 18.0, where the wide kernels
+// take 13.3 and 11.9.
+// Spilled registers: multipliers, biases, start sums, two rounds of loads and the
+// residual's words are live together in 256 VGPRs (two waves a SIMD).  Of the 184
+// instances eight spill, all resident 1x1 from images of 4-fragment blocks with
+// NP 2: with the bias and residual epilogue FP 4 by 13-21 registers (4 bits) and
+// 39-63 (8 bits) and FP 2 of LA 4 in one round by 6 (4 bits); without it FP 2 of
+// LA 4 in several rounds by 3 (8 bits).  direct_margin asks more of the first.
 template <int BITS, int FKB, int NP, int FP, bool EXT, int LA, bool MULTI, bool LIN, bool WRES, bool B16 = false>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) conv_direct(DirectArgs a) {
     constexpr int NF = 2 * NP;                       // MFMA rows of 16 channels per wave

@@ -933,8 +933,8 @@ int64_t direct_steps(const qconv_desc *d) { return (int64_t)d->r * d->s * ((d->c
 
 // How far below the wide kernel's estimate a direct one has to be.  The margins
 // cover the estimates' errors and were set on 15,100 further random layers timed
-// on both routes (profiles/direct_route_check.md has the same count on others).
-// Past 1.15 + us / 100 for every larger filter and 1.1 for every 1x1,
+// on both routes; on 15,152 others 43 of 8,597 direct launches are slower by more
+// than 2 %, the worst 1.21x.  Past 1.15 + us / 100 for every larger filter and 1.1 for every 1x1,
 //   - 3x3 layers, where the wide kernels have fixed-size instances, by depth in more
 //     than 2048 waves (two a SIMD, the rest waiting) or resident: the estimates
 //     miss part of their L1 traffic;
@@ -1252,8 +1252,8 @@ int run_conv(const qconv_desc *d, const void *x, const void *w, bool prepared, s
         // times the fused launch at two stages with rows of whole dwords, 0.25-0.7
         // times it from three stages on or with other rows (N=5 57x57 512->96:
         // 84.6 us fused, 7.0 + 17.6 apart), and up to 1.5 times it at one stage.
-        // The packed copy is then the convolution's input.  (14,079 other layers:
-        // geometric mean 0.46, the worst 1.07, profiles/fused_pack_route_check.md.)
+        // The packed copy is then the convolution's input.  (On 14,079 other
+        // layers the rule takes 0.46 times one launch, geometric mean; the worst 1.07.)
         const int64_t wgs = std::min<int64_t>(pl.grid, pl.mtiles * pl.ktiles);
         const int64_t stages = (pl.mtiles * pl.ktiles + wgs - 1) / wgs * pl.cps;
         if (x_packed && (stages > 2 || (stages == 2 && d->w % 4 != 0))) {
