@@ -8,7 +8,9 @@ The search of Sec. 3.4, restated for this implementation's schedule space:
   MFMA fragments per wave along pixels and channels, channel chunk (the
   paper's BLK-ROW/COL-WARPS, WARP-ROW/COL-TILES, CHUNK and REORDER-INNER of
   Sec. 4.1) -- plus the split-K factor and three launch knobs (workgroups per
-  CU of a persistent grid, LDS band buffers, XCD-aware block order).  Many
+  CU of a persistent grid, LDS band buffers, XCD-aware block order).  All of
+  them are the tiles' own kernels: a prepared call without a split and a
+  schedule may run a direct kernel that is faster than the best of them.  Many
   knobs do nothing for a given shape, so many schedules perform alike: the
   situation Sec. 3.4 describes.
 * Cost model: gradient-boosted trees on schedule features, fitted to the
